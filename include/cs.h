@@ -27,7 +27,7 @@
  *    CS_E_INVAL/CS_E_STATE return leaves the device untouched.
  *  - Identical inputs give bitwise identical outputs, independent of N and
  *    of which other candidates are evaluated in the same step (no atomics,
- *    fixed reduction orders, tile shapes fixed per model).
+ *    fixed reduction orders, the same in every tile shape).
  *  - Latents are float32 [C][F][H][W] per candidate, candidates contiguous.
  *    D = C*F*H*W.  Weights: see cs_model_weight_count.
  */

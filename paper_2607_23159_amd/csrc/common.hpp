@@ -139,5 +139,11 @@ template <int n> CS_DEV void wait_vm_barrier() {
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(n) : "memory");
 }
 
+// The same, also waiting for this wave's LDS accesses: past the barrier every
+// wave's earlier reads of a buffer are done and it may be refilled.
+template <int n> CS_DEV void wait_all_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n) : "memory");
+}
+
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 inline long round_up(long a, long b) { return (a + b - 1) / b * b; }

@@ -4,38 +4,29 @@
 namespace cs {
 
 // ------------------------------------------------------------- launchers
-// bf16: direct-to-LDS kernels on 16x16x32 MFMAs, 256x256 tiles, K slices of
-//       64, tile groups of 4 tile-rows: k_gemm_w4 (4 waves of 128x128, one
-//       per SIMD) and, for residual updates at short K, k_gemm_dl (8 waves
-//       of 128x64, two per SIMD).  Both sum in the same order (bitwise
-//       equal results).  K must be a multiple of 64.
+// bf16: direct-to-LDS kernels on 16x16x32 MFMAs (k_gemm_w4, k_gemm_ring), tile
+//       shape chosen per launch (choose_tile), K slices of 64, tile groups of
+//       4 tile-rows; all shapes sum in the same order (bitwise equal
+//       results).  K must be a multiple of 64.
 // fp32: register-staged kernel, 128x128 tiles, 4 waves of 64x64, K slices of 16.
-// Narrow N (head GEMM, N = patch_dim): register-staged 128x64 tiles.
-template <typename T> struct GemmCfg;
-template <> struct GemmCfg<float> {
+// Narrow N in fp32 (head GEMM, N = patch_dim): register-staged 128x64 tiles.
+struct GemmCfg {
   static constexpr int BM = 128, BN = 128, BK = 16, WM = 64, WN = 64, NW = 4, OCC = 1, GM = 1;
 };
-template <typename T> struct GemmCfgNarrow;
-template <> struct GemmCfgNarrow<bf16> {
-  static constexpr int BM = 128, BN = 64, BK = 32, WM = 32, WN = 64, NW = 4, OCC = 1, GM = 1;
-};
-template <> struct GemmCfgNarrow<float> {
+struct GemmCfgNarrow {
   static constexpr int BM = 128, BN = 64, BK = 16, WM = 32, WN = 64, NW = 4, OCC = 1, GM = 1;
 };
-struct DlCfg {
-  static constexpr int BM = 256, BN = 256, BK = 64, WM = 128, WN = 64, NW = 8, OCC = 2, ST = 2,
-                       GM = 4;
-};
+constexpr int BF16_BK = 64, BF16_GM = 4;
 
 // ------------------------------------------------------- weight tiling
-// bf16 weights for the direct-load kernel: [N][K] fp32 row-major ->
-// blocks of DlCfg::BN rows x DlCfg::BK columns, block (tn, kt) at
+// bf16 weights for the direct-load kernels: [N][K] fp32 row-major ->
+// blocks of W_BLOCK_ROWS rows x BF16_BK columns, block (tn, kt) at
 // ((tn * K/BK + kt) * BN * BK) elements; inside a block row r holds its 8
 // chunks of 8 columns with logical chunk c at physical position
 // c ^ gemm_swz(r), the LDS layout of the kernel.  Rows past N are zero.
 __global__ __launch_bounds__(256) void k_tile_weight(const float* __restrict__ src, int N, int K,
                                                      bf16* __restrict__ dst, long n_chunks) {
-  constexpr int BN = DlCfg::BN, BK = DlCfg::BK, CPR = BK / 8;
+  constexpr int BN = W_BLOCK_ROWS, BK = BF16_BK, CPR = BK / 8;
   const long q = (long)blockIdx.x * 256 + threadIdx.x;
   if (q >= n_chunks) return;
   const long blk = q / (BN * CPR);
@@ -51,10 +42,10 @@ __global__ __launch_bounds__(256) void k_tile_weight(const float* __restrict__ s
   *reinterpret_cast<bf16x8*>(dst + q * 8) = v;
 }
 
-long gemm_tiled_weight_elems(int N, int K) { return round_up(N, DlCfg::BN) * (long)K; }
+long gemm_tiled_weight_elems(int N, int K) { return round_up(N, W_BLOCK_ROWS) * (long)K; }
 
 hipError_t gemm_tile_weight(const float* src, int N, int K, bf16* dst, hipStream_t st) {
-  if (N <= 0 || K % DlCfg::BK != 0) return hipErrorInvalidValue;
+  if (N <= 0 || K % BF16_BK != 0) return hipErrorInvalidValue;
   const long n_chunks = gemm_tiled_weight_elems(N, K) / 8;
   hipLaunchKernelGGL(k_tile_weight, dim3((unsigned)cdiv(n_chunks, 256)), dim3(256), 0, st, src, N, K, dst,
                      n_chunks);
@@ -72,38 +63,114 @@ static hipError_t launch_staged(const T* A, long lda, const T* W, long ldw, int 
   return hipGetLastError();
 }
 
-// Residual-update epilogues read and write the fp32 residual stream: at
-// short K their epilogue, not the products, sets the pace, and eight waves
-// per CU (k_gemm_dl) keep more of those reads in flight than four.  Measured
-// crossover: k_gemm_dl is 8% faster at K = 1536 and 2% at K = 3072, k_gemm_w4
-// 4% faster at K = 5120 and 9% at K = 14336.
+// ------------------------------------------------------ bf16 tile choice
+// Residual updates read and write the fp32 residual stream in their epilogue,
+// which then weighs several times a bf16 store.
 template <class Epi> struct EpiIsResidual : std::false_type {};
 template <int G> struct EpiIsResidual<EpiResidual<G>> : std::true_type {};
 template <int G, typename T> struct EpiIsResidual<EpiResidualStore<G, T>> : std::true_type {};
-constexpr int W4_MIN_RESIDUAL_K = 4096;
+// The transposed part of the QKV epilogue needs power-of-two wave tiles.
+template <class Epi> struct EpiAllows192 : std::true_type {};
+template <typename T> struct EpiAllows192<EpiQKV<T>> : std::false_type {};
+
+enum Bf16Tile { W4_256x256, W4_192x256, W4_128x256, W4_128x128, W4_64x64, RING_64x64, RING_32x64, RING_32x32, N_TILES };
+
+// Time of a launch per tile shape, in us:
+//   fixed + rounds * (K/64 * full + epi) + K/64 * (lone + (full - lone) * r) + epi * (1 + r) / 2
+// where a round fills `slots` workgroups on each of the 256 CUs, r is the
+// filled part of the last round (left out when 0), `lone` and `full` are the
+// time per K slice of 64 of a tile alone on its CU and of a full chip, and epi
+// grows by epi_res for residual updates.  The constants are a least-squares
+// fit to 428 measured shapes (64 to 65,520 rows; N and K of the tiny, ragged,
+// 1.3B, 5B and 14B projections; bf16 stores and residual updates) that
+// reproduces each shape's times within 4 to 11%.  The choice it makes costs
+// 1.5% on average over those 428 (at most 24%, at launches under 20 us)
+// against the best tile of each, where 256 x 256 tiles for everything took 2.3
+// times as long on average.
+struct TileCost { int bm, bn, slots; double lone, full, fixed, epi, epi_res; };
+static const TileCost TILE_COST[N_TILES] = {
+    {256, 256, 1, 0.907, 1.336, 3.32, 7.90, 16.5},
+    {192, 256, 1, 0.720, 1.038, 2.87, 6.32, 11.0},
+    {128, 256, 1, 0.544, 0.761, 2.57, 4.42, 7.19},
+    {128, 128, 2, 0.326, 0.838, 1.83, 3.39, 4.53},
+    {64, 64, 3, 0.183, 0.531, 1.96, 1.20, 1.30},
+    {64, 64, 1, 0.187, 0.204, 1.91, 1.53, 0.61},
+    {32, 64, 2, 0.137, 0.248, 2.09, 1.06, 0.50},
+    {32, 32, 2, 0.113, 0.203, 2.02, 0.79, 0.16},
+};
+// From two rounds of 256 x 256 tiles on, the chip's power limit evens out a
+// partly filled last round (idle CUs let the others clock higher), so only 192
+// x 256 competes, and only with 3% in hand: 43,680 x 3072 x 3072 (8.02 rounds)
+// takes 775 us with 192 rows against 819, but 262,080 rows (24 rounds) 1% more.
+// Narrow outputs (the head) would leave most of a 256-wide tile empty.
+constexpr long LARGE_TILES = 512, LARGE_MIN_N = 1024;
+constexpr double LARGE_MARGIN = 0.97;
+
+static Bf16Tile choose_tile(long M, long N, long K, bool residual, bool allow_192) {
+  const double nk = (double)(K / BF16_BK);
+  auto cost = [&](int i) {
+    const TileCost& c = TILE_COST[i];
+    const long tiles = (long)cdiv(M, c.bm) * cdiv(N, c.bn), round = 256L * c.slots;
+    const double epi = c.epi + (residual ? c.epi_res : 0.0), r = (double)(tiles % round) / (double)round;
+    double t = c.fixed + (double)(tiles / round) * (nk * c.full + epi);
+    if (r > 0) t += nk * (c.lone + (c.full - c.lone) * r) + epi * 0.5 * (1.0 + r);
+    return t;
+  };
+  const long tiles256 = (long)cdiv(M, 256) * cdiv(N, 256);
+  if (tiles256 >= LARGE_TILES && N >= LARGE_MIN_N)
+    return allow_192 && cost(W4_192x256) < LARGE_MARGIN * cost(W4_256x256) ? W4_192x256 : W4_256x256;
+  int best = W4_256x256;
+  double best_t = cost(best);
+  for (int i = 0; i < N_TILES; ++i) {
+    if (i == W4_192x256 && !allow_192) continue;
+    const double t = cost(i);
+    if (t < best_t) { best = i; best_t = t; }
+  }
+  return (Bf16Tile)best;
+}
+
+template <int BM, int BN, int OCC, int PD, class Epi>
+static void launch_w4(const bf16* A, long lda, const bf16* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
+  const unsigned tiles = (unsigned)((long)cdiv(M, BM) * cdiv(N, BN));
+  hipLaunchKernelGGL((k_gemm_w4<BM, BN, OCC, BF16_GM, PD, Epi>), dim3(tiles), dim3(256), 0, st, A, lda, W, M, N, K,
+                     epi);
+}
+
+template <int BM, int BN, int WGM, int WGN, int STAGES, class Epi>
+static void launch_ring(const bf16* A, long lda, const bf16* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
+  const unsigned tiles = (unsigned)((long)cdiv(M, BM) * cdiv(N, BN));
+  hipLaunchKernelGGL((k_gemm_ring<BM, BN, WGM, WGN, STAGES, 2, BF16_GM, Epi>), dim3(tiles), dim3(64 * WGM * WGN), 0,
+                     st, A, lda, W, M, N, K, epi);
+}
 
 template <typename T, class Epi>
 static hipError_t launch(const T* A, long lda, const T* W, long ldw, int M, int N, int K, Epi epi,
                          hipStream_t st) {
   if constexpr (sizeof(T) == 2) {
-    typedef DlCfg C;
     if (M <= 0 || N <= 0) return hipSuccess;
-    if (K <= 0 || K % C::BK != 0 || N % 4 != 0) return hipErrorInvalidValue;
+    if (K <= 0 || K % BF16_BK != 0 || N % 4 != 0) return hipErrorInvalidValue;
     // W is pre-tiled (row stride K); per-tile buffer ranges are 32-bit byte counts
     if (ldw != K) return hipErrorInvalidValue;
-    if ((long)std::max(C::BM, C::BN) * std::max(lda, (long)K) * 2 > 0x7FFFFFFFL) return hipErrorInvalidValue;
-    const long tiles = (long)cdiv(M, C::BM) * cdiv(N, C::BN);
-    if (EpiIsResidual<Epi>::value && K < W4_MIN_RESIDUAL_K) {
-      hipLaunchKernelGGL((k_gemm_dl<C::BM, C::BN, C::BK, C::WM, C::WN, C::NW, C::OCC, C::ST, C::GM, Epi>),
-                         dim3((unsigned)tiles), dim3(64 * C::NW), 0, st, A, lda, W, ldw, M, N, K, epi);
-    } else {
-      constexpr int PD = EpiIsResidual<Epi>::value ? 8 : 2;
-      hipLaunchKernelGGL((k_gemm_w4<C::BM, C::GM, PD, Epi>), dim3((unsigned)tiles), dim3(256), 0, st, A,
-                         lda, W, ldw, M, N, K, epi);
+    if ((long)W_BLOCK_ROWS * std::max(lda, (long)K) * 2 > 0x7FFFFFFFL) return hipErrorInvalidValue;
+    constexpr bool RES = EpiIsResidual<Epi>::value, A192 = EpiAllows192<Epi>::value;
+    // residual operands in flight per wave: with one wave per SIMD nothing
+    // else hides their latency, with two workgroups per CU half as many do
+    constexpr int PD = RES ? 8 : 2, PD2 = RES ? 4 : 2;
+    switch (choose_tile(M, N, K, RES, A192)) {
+      case W4_256x256: launch_w4<256, 256, 1, PD>(A, lda, W, M, N, K, epi, st); break;
+      case W4_192x256:
+        if constexpr (A192) launch_w4<192, 256, 1, PD>(A, lda, W, M, N, K, epi, st);
+        break;
+      case W4_128x256: launch_w4<128, 256, 1, PD>(A, lda, W, M, N, K, epi, st); break;
+      case W4_128x128: launch_w4<128, 128, 2, PD2>(A, lda, W, M, N, K, epi, st); break;
+      case W4_64x64: launch_w4<64, 64, 3, 2>(A, lda, W, M, N, K, epi, st); break;
+      case RING_64x64: launch_ring<64, 64, 2, 4, 4>(A, lda, W, M, N, K, epi, st); break;
+      case RING_32x64: launch_ring<32, 64, 1, 4, 3>(A, lda, W, M, N, K, epi, st); break;
+      default: launch_ring<32, 32, 2, 2, 4>(A, lda, W, M, N, K, epi, st);
     }
     return hipGetLastError();
   } else {
-    return launch_staged<T, GemmCfg<T>>(A, lda, W, ldw, M, N, K, epi, st);
+    return launch_staged<T, GemmCfg>(A, lda, W, ldw, M, N, K, epi, st);
   }
 }
 
@@ -153,7 +220,11 @@ hipError_t gemm_head(const T* A, const T* W, int M, int d, int P, const float* b
                      const int* slot_id, int L, int gh, int gw, int F, int H, int Wd, long D,
                      hipStream_t st) {
   EpiHead e{out, slot_id, bias, L, gh, gw, F, H, Wd, D};
-  return launch_staged<T, GemmCfgNarrow<T>>(A, d, W, d, M, P, d, e, st);
+  if constexpr (sizeof(T) == 2) {
+    return launch<T>(A, d, W, d, M, P, d, e, st);
+  } else {
+    return launch_staged<T, GemmCfgNarrow>(A, d, W, d, M, P, d, e, st);
+  }
 }
 
 #define CS_INST(T)                                                                              \

@@ -592,11 +592,11 @@ static cs_status model_init_impl(const cs_model_desc* desc, const float* weights
 
   // arena: matrices in the compute type, vectors fp32; block modulation
   // tables gathered into one [n_blocks][6][d] array.  In bf16 the weights of
-  // the direct-load GEMM (every matrix except the three time-conditioning
-  // GEMV matrices and the narrow head) are stored in its tiled layout.
+  // the direct-load GEMMs (every matrix except the three time-conditioning
+  // GEMV matrices) are stored in their tiled layout.
   auto tiled = [&](const TSpec& t) {
     return m->esz == 2 && t.matrix && t.name != "time1_w" && t.name != "time2_w" &&
-           t.name != "mod_w" && t.name != "head_w";
+           t.name != "mod_w";
   };
   std::vector<size_t> off(spec.size());
   size_t bytes = 0;
