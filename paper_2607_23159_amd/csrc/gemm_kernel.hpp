@@ -2,18 +2,17 @@
 //
 //   C[M][N] = A[M][K] * W[N][K]^T   (A row-major, W = weights [out][in])
 //
-// k_gemm (fp32): one workgroup computes a BM x BN tile; each wave owns a WM x
-// WN sub-tile made of 32x32 MFMA accumulators.  K is walked in BK slices that
-// are staged through LDS (double buffered, one barrier per slice; the next
-// slice's global loads are in flight while the current slice is multiplied).
-// Rows of the LDS tiles are padded by 16 bytes so that the 16-byte fragment
-// reads of 32 consecutive rows fall in distinct banks.  Ragged M and N tails
-// are handled by clamping the load row (valid memory) and masking stores.
-// k_gemm_w4 and k_gemm_ring (bf16): see there.
+// Two kernels on direct global->LDS loads: k_gemm_w4 (bf16) and k_gemm_ring
+// (bf16 and fp32); ragged M and N tails are handled by the loads' buffer ranges
+// (zeros) and by masking stores.
 //
 // The accumulation order over K depends on the element type only, never on the
-// tile shape or on M: a row's result is bitwise the same whatever other rows
-// share the launch (batch invariance).
+// kernel, the tile shape or M: a row's result is bitwise the same whatever
+// other rows share the launch (batch invariance).
+//
+// Every projection of the model has a bias; the accumulators start from it
+// (each column's bias, then the products in a fixed K order), so the epilogue
+// reads no bias.
 #pragma once
 #include "kernels.hpp"
 
@@ -21,102 +20,7 @@
 
 namespace cs {
 
-template <typename T, int BM, int BN, int BK, int WM, int WN, int NWAVE>
-struct GemmShape {
-  static constexpr int NT = 64 * NWAVE;            // threads per workgroup
-  static constexpr int CH = 16 / (int)sizeof(T);   // elements per 16-byte chunk
-  static constexpr int LDS_LD = BK + CH;           // padded LDS row
-  static constexpr int WAVES_N = BN / WN;
-  static constexpr int WAVES_M = BM / WM;
-  static constexpr int TM = WM / 32;
-  static constexpr int TN = WN / 32;
-  static constexpr int CPR = BK / CH;              // chunks per row of a slice
-  static constexpr int A_CH = BM * CPR / NT;       // chunks per thread
-  static constexpr int B_CH = BN * CPR / NT;
-  static constexpr int KS = BK / Mfma32<T>::KSTEP; // MFMA k-steps per slice
-  static_assert(WAVES_N * WAVES_M == NWAVE, "wave grid");
-  static_assert(A_CH * NT == BM * CPR && B_CH * NT == BN * CPR, "slice split");
-};
-
-// Accumulator layout of the register-staged kernel: the products are formed as C^T
-// tiles (W fragment as the MFMA A operand), so accumulator (i, j) of a lane
-// holds row i*32 + lane%32 of the wave's sub-tile and, in register 4g + r,
-// column j*32 + 8g + 4(lane/32) + r.  Every group of 4 registers is 4
-// consecutive columns of one row, i.e. one vector access in the epilogue.
-//
-// Every projection of the model has a bias; the accumulators start from it
-// (each column's bias, then the products in a fixed K order), so the
-// epilogue reads no bias.
-template <int TM, int TN>
-CS_DEV void init_acc_bias(f32x16 (&acc)[TM][TN], const float* __restrict__ bias, int col_base,
-                          int lane, int N) {
-#pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col0 = col_base + j * 32 + 8 * g + 4 * (lane >> 5);
-      float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (col0 < N) b = *reinterpret_cast<const float4*>(bias + col0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        acc[i][j][4 * g] = b.x;
-        acc[i][j][4 * g + 1] = b.y;
-        acc[i][j][4 * g + 2] = b.z;
-        acc[i][j][4 * g + 3] = b.w;
-      }
-    }
-}
-
-// Epilogue over the wave's accumulators, in chunks of one accumulator (4
-// groups of 4 columns).  The operands an epilogue reads (Epi::pre: residual
-// and gate) are requested one chunk ahead of the chunk being stored, so their
-// latency overlaps the previous chunk's arithmetic and stores instead of
-// stalling every group.  A wave whose sub-tile lies inside [0,M) x [0,N)
-// (all but the tail tiles) takes a copy without bounds checks: straight-line
-// code lets the compiler wait for exactly the loads it needs, where branches
-// around each access would make it wait for all outstanding memory traffic.
-template <bool CHECK, int TM, int TN, class Epi>
-CS_DEV void gemm_epilogue_impl(const f32x16 (&acc)[TM][TN], int row_base, int col_base, int lane,
-                               int M, int N, const Epi& epi) {
-  constexpr int NQ = TM * TN;
-  typename Epi::Pre pre[2][4];
-  auto fetch = [&](int q, int slot) {
-    const int i = q / TN, j = q % TN;
-    const int row = row_base + i * 32 + (lane & 31);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col0 = col_base + j * 32 + 8 * g + 4 * (lane >> 5);
-      if (!CHECK || (row < M && col0 < N)) pre[slot][g] = epi.pre(row, col0);
-    }
-  };
-  fetch(0, 0);
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    if (q + 1 < NQ) fetch(q + 1, (q + 1) & 1);
-    const int i = q / TN, j = q % TN;
-    const int row = row_base + i * 32 + (lane & 31);
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col0 = col_base + j * 32 + 8 * g + 4 * (lane >> 5);
-      if (!CHECK || (row < M && col0 < N)) {
-        const float v[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                            acc[i][j][4 * g + 3]};
-        epi(row, col0, v, pre[q & 1][g]);
-      }
-    }
-  }
-}
-
-template <int TM, int TN, class Epi>
-CS_DEV void gemm_epilogue(const f32x16 (&acc)[TM][TN], int row_base, int col_base, int lane,
-                          int M, int N, const Epi& epi) {
-  if (row_base + TM * 32 <= M && col_base + TN * 32 <= N)
-    gemm_epilogue_impl<false>(acc, row_base, col_base, lane, M, N, epi);
-  else
-    gemm_epilogue_impl<true>(acc, row_base, col_base, lane, M, N, epi);
-}
-
-// LDS layout of the direct-load bf16 kernels: a tile row holds 64 bf16 (8
+// LDS layout: a tile row holds 128 bytes of one K slice (64 bf16 or 32 fp32, 8
 // chunks of 16 bytes); logical chunk c of row r is stored at c ^ gemm_swz(r),
 // gemm_swz(r) = r mod 8.  A fragment read (16 rows, each lane one 16-byte
 // chunk) measured free of LDS bank conflicts with this swizzle (a variant
@@ -126,8 +30,8 @@ CS_DEV void gemm_epilogue(const f32x16 (&acc)[TM][TN], int row_base, int col_bas
 // by an immediate offset.
 CS_DEV int gemm_swz(int r) { return r & 7; }
 
-// 16x16 accumulators of the bf16 kernel (v_mfma_f32_16x16x32_bf16), also
-// formed as C^T tiles: accumulator (i, j) of a lane holds row i*16 + lane%16
+// 16x16 accumulators: the products are formed as C^T tiles (W fragment as the
+// MFMA A operand), so accumulator (i, j) of a lane holds row i*16 + lane%16
 // of the wave's sub-tile and, in registers 0..3, columns j*16 + 4(lane/16) ..
 // +3, one vector access in the epilogue.
 template <int TM, int TN>
@@ -146,132 +50,6 @@ CS_DEV void init_acc16_bias(f32x4 (&acc)[TM][TN], const float* __restrict__ bias
       acc[i][j][3] = b.w;
     }
   }
-}
-
-// OCC = waves per SIMD the register budget is sized for; GM = tile-rows per
-// group of the tile order (1 = row-major).
-template <typename T, int BM, int BN, int BK, int WM, int WN, int NWAVE, int OCC, int GM, class Epi>
-__global__ __launch_bounds__(64 * NWAVE, OCC) void k_gemm(const T* __restrict__ A, long lda,
-                                                        const T* __restrict__ W, long ldw, int M,
-                                                        int N, int K, Epi epi) {
-  typedef GemmShape<T, BM, BN, BK, WM, WN, NWAVE> S;
-  typedef Mfma32<T> MF;
-  constexpr int KPL = MF::KPL, KSTEP = MF::KSTEP;
-  __shared__ __attribute__((aligned(16))) T sA[2][BM * S::LDS_LD];
-  __shared__ __attribute__((aligned(16))) T sB[2][BN * S::LDS_LD];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave / S::WAVES_N, wn = wave % S::WAVES_N;
-
-  // Tile order: the launch is split into 8 contiguous ranges, one per XCD
-  // (workgroups are dealt round-robin to the 8 dies).  Inside a range, tiles
-  // are visited in groups of GM tile-rows, column-major within the group, so
-  // the workgroups resident on one die at a time share both rows of A and
-  // columns of W in its L2.
-  const int tiles_n = (N + BN - 1) / BN;
-  const int tiles_m = (M + BM - 1) / BM;
-  const int nwg = gridDim.x;
-  const int bid = xcd_contiguous(blockIdx.x, nwg);
-  int tm_i, tn_i;
-  if (GM > 1) {
-    const int group = bid / (GM * tiles_n);
-    const int first_m = group * GM;
-    const int gm = min(tiles_m - first_m, GM);
-    const int in = bid - group * GM * tiles_n;
-    tm_i = first_m + in % gm;
-    tn_i = in / gm;
-  } else {
-    tm_i = bid / tiles_n;
-    tn_i = bid % tiles_n;
-  }
-  const int m0 = tm_i * BM;
-  const int n0 = tn_i * BN;
-
-  // global -> register staging
-  Chunk16 ra[S::A_CH], rb[S::B_CH];
-  const T* a_src[S::A_CH];
-  const T* b_src[S::B_CH];
-  int a_dst[S::A_CH], b_dst[S::B_CH];
-#pragma unroll
-  for (int c = 0; c < S::A_CH; ++c) {
-    int id = c * S::NT + tid;
-    int r = id / S::CPR, cc = id % S::CPR;
-    int gr = min(m0 + r, M - 1);
-    a_src[c] = A + (long)gr * lda + cc * S::CH;
-    a_dst[c] = r * S::LDS_LD + cc * S::CH;
-  }
-#pragma unroll
-  for (int c = 0; c < S::B_CH; ++c) {
-    int id = c * S::NT + tid;
-    int r = id / S::CPR, cc = id % S::CPR;
-    int gr = min(n0 + r, N - 1);
-    b_src[c] = W + (long)gr * ldw + cc * S::CH;
-    b_dst[c] = r * S::LDS_LD + cc * S::CH;
-  }
-
-  f32x16 acc[S::TM][S::TN];
-  init_acc_bias(acc, epi.bias, n0 + wn * WN, lane, N);
-
-  const int nk = K / BK;
-#pragma unroll
-  for (int c = 0; c < S::A_CH; ++c) ra[c] = ld16(a_src[c]);
-#pragma unroll
-  for (int c = 0; c < S::B_CH; ++c) rb[c] = ld16(b_src[c]);
-#pragma unroll
-  for (int c = 0; c < S::A_CH; ++c) st16(&sA[0][a_dst[c]], ra[c]);
-#pragma unroll
-  for (int c = 0; c < S::B_CH; ++c) st16(&sB[0][b_dst[c]], rb[c]);
-  __syncthreads();
-
-  const int frag_k = KPL * (lane >> 5);
-  const int a_row = wm * WM + (lane & 31);
-  const int b_row = wn * WN + (lane & 31);
-
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) {
-      const long koff = (long)(kt + 1) * BK;
-#pragma unroll
-      for (int c = 0; c < S::A_CH; ++c) ra[c] = ld16(a_src[c] + koff);
-#pragma unroll
-      for (int c = 0; c < S::B_CH; ++c) rb[c] = ld16(b_src[c] + koff);
-    }
-    const T* pa = &sA[cur][a_row * S::LDS_LD + frag_k];
-    const T* pb = &sB[cur][b_row * S::LDS_LD + frag_k];
-    // fragments of k-step ks+1 are read while the products of ks issue
-    typename MF::frag fa[2][S::TM], fb[2][S::TN];
-#pragma unroll
-    for (int i = 0; i < S::TM; ++i) fa[0][i] = MF::load(pa + i * 32 * S::LDS_LD);
-#pragma unroll
-    for (int j = 0; j < S::TN; ++j) fb[0][j] = MF::load(pb + j * 32 * S::LDS_LD);
-#pragma unroll
-    for (int ks = 0; ks < S::KS; ++ks) {
-      const int c = ks & 1, n = c ^ 1;
-      if (ks + 1 < S::KS) {
-#pragma unroll
-        for (int i = 0; i < S::TM; ++i) fa[n][i] = MF::load(pa + i * 32 * S::LDS_LD + (ks + 1) * KSTEP);
-#pragma unroll
-        for (int j = 0; j < S::TN; ++j) fb[n][j] = MF::load(pb + j * 32 * S::LDS_LD + (ks + 1) * KSTEP);
-      }
-#pragma unroll
-      for (int i = 0; i < S::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < S::TN; ++j) acc[i][j] = MF::mma(fb[c][j], fa[c][i], acc[i][j]);
-    }
-    if (more) {
-      const int nxt = cur ^ 1;
-#pragma unroll
-      for (int c = 0; c < S::A_CH; ++c) st16(&sA[nxt][a_dst[c]], ra[c]);
-#pragma unroll
-      for (int c = 0; c < S::B_CH; ++c) st16(&sB[nxt][b_dst[c]], rb[c]);
-    }
-    __syncthreads();
-  }
-
-  gemm_epilogue(acc, m0 + wm * WM, n0 + wn * WN, lane, M, N, epi);
 }
 
 // Epilogue over 16x16 accumulators with the epilogue operands of PD - 1
@@ -313,29 +91,33 @@ CS_DEV void gemm_epilogue16_deep(const f32x4 (&acc)[TM][TN], int row_base, int c
 }
 
 // ---------------------------------------------------------------------------
-// The bf16 GEMMs: direct global->LDS loads (gfx950 buffer_load_dwordx4 ...
-// lds) and 16x16x32 MFMAs.
+// Direct global->LDS loads (gfx950 buffer_load_dwordx4 ... lds) and 16x16
+// MFMAs (x32 in bf16, x4 in fp32).
 //
 // Each load instruction of a wave moves 64 x 16 bytes into 1 KB of LDS at
 // base + 16*lane, with an arbitrary source offset per lane, so no registers
 // stage the tiles and no LDS store instructions are issued.  LDS rows are
 // unpadded and swizzled (gemm_swz), which keeps the fragment reads (16 rows x
 // 4 chunks per instruction) free of bank conflicts.  W is stored in blocks of
-// 256 rows x 64 columns (gemm_tile_weight); a tile of BN < 256 columns takes
+// 256 rows x 128 bytes (gemm_tile_weight); a tile of BN < 256 columns takes
 // BN consecutive rows of a block, which are contiguous there.
 //
-// Two kernels, one per limit.  k_gemm_w4 (below) is for tiles whose products
-// fill the matrix pipe; k_gemm_ring (further down) for grids that leave most
-// CUs with a single small tile, where the latency from one K slice to the
-// next is what counts.  Every tile shape of both sums in the same order (bias,
-// then K in steps of 32), so results are bitwise equal whichever is chosen:
-// the choice (choose_tile in k_gemm.hip) may follow M without making a row's
-// result depend on how many other rows share the launch.
+// Two kernels, one per limit.  k_gemm_w4 (below) is for bf16 tiles whose
+// products fill the matrix pipe; k_gemm_ring (further down) for grids that
+// leave most CUs with a single small tile, where the latency from one K slice
+// to the next is what counts, and for fp32, whose products take 16 times as
+// long per byte loaded.  In either type every tile shape sums in the same order
+// (bias, then K in steps of 32 in bf16, of 16 in fp32), so results are bitwise
+// equal whichever is chosen: the choice (k_gemm.hip) may follow M without
+// making a row's result depend on how many other rows share the launch.
 // ---------------------------------------------------------------------------
 constexpr int W_BLOCK_ROWS = 256;   // rows of a block of the tiled weights
 
-// Tile of a workgroup in the XCD-contiguous order of groups of GM tile-rows
-// (column-major within a group; see k_gemm).
+// Tile order: the launch is split into 8 contiguous ranges, one per XCD
+// (workgroups are dealt round-robin to the 8 dies).  Inside a range, tiles are
+// visited in groups of GM tile-rows, column-major within the group, so the
+// workgroups resident on one die at a time share both rows of A and columns of
+// W in its L2.
 template <int GM>
 CS_DEV void gemm_tile_of(int tiles_m, int tiles_n, int& tm_i, int& tn_i) {
   const int bid = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -560,8 +342,9 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_w4(const bf16* __restrict__ A
 }
 
 // ---------------------------------------------------------------------------
-// bf16 GEMM for small grids (few rows, narrow outputs): BM x BN tiles of 64 x
-// 64 (8 waves of 32 x 16), 32 x 64 and 32 x 32 (4 waves).
+// GEMM on a ring of LDS stages.  In bf16 for small grids (few rows, narrow
+// outputs): BM x BN tiles of 64 x 64 (8 waves of 32 x 16), 32 x 64 and 32 x 32
+// (4 waves).  In fp32 for all of them.
 //
 // With a tile or less per CU nothing runs beside it, so a slice costs its
 // latency chain: barrier, fragment reads, products.  The chain is shortened in
@@ -573,12 +356,40 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_w4(const bf16* __restrict__ A
 // tokens on the 1.3B FFN-down projection, 144 tiles of 64 x 64: 30 us, against
 // 156 us with 256 x 256 tiles (12 of them) and 41 us with one slice per
 // barrier; 891 x 256 x 512 with 32 x 32 tiles: 3.4 us against 24.8 us.
+//
+// In fp32 a 32 x 32 x 32 slice of products takes 256 cycles per CU, ten times
+// the fragment reads, and the matrix pipe is the limit whatever the tile: the
+// smallest tile wins by filling the chip evenly, with four workgroups per CU
+// covering each other's barriers.  768 x 1536 x 8960: 183 us (115 TFLOP/s),
+// against 391 us (up to 660) with 128 x 128 register-staged tiles; 1024 x 128 x
+// 512: 5.1 against 43 us.  A lane's 16-byte chunk holds four consecutive k;
+// product e of a chunk takes element e of the four lanes of a row, so four
+// products consume a chunk of each operand without any shuffle.  The distance
+// of whole evaluations and rollouts to 64-bit results (8 shapes, 8 seeds each)
+// is that of sums in natural k order: 4.4e-7 at d = 128, 1.45e-6 at d = 1536.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int GM, class Epi>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const bf16* __restrict__ A, long lda,
-                                                                  const bf16* __restrict__ W, int M,
+template <typename T> struct Mfma16;
+template <> struct Mfma16<bf16> {
+  typedef bf16x8 chunk;
+  static CS_DEV f32x4 mma(const chunk& a, const chunk& b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct Mfma16<float> {
+  typedef f32x4 chunk;
+  static CS_DEV f32x4 mma(const chunk& a, const chunk& b, f32x4 c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+    return c;
+  }
+};
+
+template <typename T, int BM, int BN, int WGM, int WGN, int SL, int STAGES, int OCC, int GM, class Epi>
+__global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __restrict__ A, long lda,
+                                                                  const T* __restrict__ W, int M,
                                                                   int N, int K, Epi epi) {
-  constexpr int BK = 64, CH = 8, RPI = 8, SL = 2, NWAVE = WGM * WGN;
+  typedef typename Mfma16<T>::chunk chunk;
+  constexpr int ES = (int)sizeof(T), CH = 16 / ES, BK = 8 * CH, RPI = 8, NWAVE = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, NF = TM + TN;
   constexpr int A_INST = BM / RPI / NWAVE, B_INST = BN / RPI / NWAVE;
   constexpr int PER = (A_INST + B_INST) * SL;               // load instructions per wave per step
@@ -586,7 +397,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const bf16* _
   static_assert(A_INST * RPI * NWAVE == BM && B_INST * RPI * NWAVE == BN, "load split");
   static_assert(W_BLOCK_ROWS % BN == 0, "part of a tiled W block");
   static_assert(STAGES >= 2 && STAGES <= 4, "wait counts below");
-  __shared__ __attribute__((aligned(1024))) bf16 smem[STAGES * STAGE];
+  __shared__ __attribute__((aligned(1024))) T smem[STAGES * STAGE];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
@@ -597,15 +408,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const bf16* _
   const int m0 = tm_i * BM, n0 = tn_i * BN;
 
   // operand ranges and per-lane offsets as in k_gemm_w4
-  const bf16* a_base = A + (long)m0 * lda;
+  const T* a_base = A + (long)m0 * lda;
   const int n_in = n0 % W_BLOCK_ROWS;
-  const bf16* b_base = W + (long)(n0 - n_in) * K + n_in * BK;
-  const int a_bytes = min(BM, M - m0) * (int)lda * 2, b_bytes = (W_BLOCK_ROWS * K - n_in * BK) * 2;
+  const T* b_base = W + (long)(n0 - n_in) * K + n_in * BK;
+  const int a_bytes = min(BM, M - m0) * (int)lda * ES, b_bytes = (W_BLOCK_ROWS * K - n_in * BK) * ES;
   int a_off[A_INST], b_off[B_INST];
 #pragma unroll
   for (int i = 0; i < A_INST; ++i) {
     const int row = (wave * A_INST + i) * RPI + lane / 8;
-    a_off[i] = (row * (int)lda + ((lane % 8) ^ gemm_swz(row)) * CH) * 2;
+    a_off[i] = (row * (int)lda + ((lane % 8) ^ gemm_swz(row)) * CH) * ES;
   }
 #pragma unroll
   for (int i = 0; i < B_INST; ++i) b_off[i] = (wave * B_INST + i) * 1024 + lane * 16;
@@ -615,16 +426,16 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const bf16* _
   auto issue = [&](int step, int st) {
 #pragma unroll
     for (int l = 0; l < SL; ++l) {
-      bf16* sa = smem + st * STAGE + l * SLICE;
-      bf16* sb = sa + BM * BK;
+      T* sa = smem + st * STAGE + l * SLICE;
+      T* sb = sa + BM * BK;
       const int slice = min(step * SL + l, nslice - 1);
 #pragma unroll
       for (int i = 0; i < A_INST; ++i)
-        buffer_load_lds16(a_base, a_bytes, sa + (wave * A_INST + i) * RPI * BK, a_off[i], slice * BK * 2);
+        buffer_load_lds16(a_base, a_bytes, sa + (wave * A_INST + i) * RPI * BK, a_off[i], slice * BK * ES);
 #pragma unroll
       for (int i = 0; i < B_INST; ++i)
         buffer_load_lds16(b_base, b_bytes, sb + (wave * B_INST + i) * RPI * BK, b_off[i],
-                          slice * W_BLOCK_ROWS * BK * 2);
+                          slice * W_BLOCK_ROWS * BK * ES);
     }
   };
 
@@ -641,33 +452,33 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const bf16* _
                         a_row0 * BK + ((4 + quad) ^ gemm_swz(a_row0)) * CH};
   const int b_lds[2] = {(BM + b_row0) * BK + (quad ^ gemm_swz(b_row0)) * CH,
                         (BM + b_row0) * BK + ((4 + quad) ^ gemm_swz(b_row0)) * CH};
-  bf16x8 f[2][2 * SL][NF];   // two register sets of one step's fragments
-  auto read = [&](int st, bf16x8(&o)[2 * SL][NF]) {
+  chunk f[2][2 * SL][NF];   // two register sets of one step's fragments
+  auto read = [&](int st, chunk(&o)[2 * SL][NF]) {
 #pragma unroll
     for (int ks = 0; ks < 2 * SL; ++ks) {
-      const bf16* s = smem + st * STAGE + (ks >> 1) * SLICE;
+      const T* s = smem + st * STAGE + (ks >> 1) * SLICE;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) o[ks][TM + j] = *reinterpret_cast<const bf16x8*>(s + b_lds[ks & 1] + j * 16 * BK);
+      for (int j = 0; j < TN; ++j) o[ks][TM + j] = *reinterpret_cast<const chunk*>(s + b_lds[ks & 1] + j * 16 * BK);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) o[ks][i] = *reinterpret_cast<const bf16x8*>(s + a_lds[ks & 1] + i * 16 * BK);
+      for (int i = 0; i < TM; ++i) o[ks][i] = *reinterpret_cast<const chunk*>(s + a_lds[ks & 1] + i * 16 * BK);
     }
   };
-  auto mul = [&](int step, const bf16x8(&o)[2 * SL][NF]) {
+  auto mul = [&](int step, const chunk(&o)[2 * SL][NF]) {
 #pragma unroll
     for (int ks = 0; ks < 2 * SL; ++ks) {
-      if (ks == 2 && step * SL + 1 >= nslice) break;
+      if (SL == 2 && ks == 2 && step * SL + 1 >= nslice) break;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o[ks][TM + j], o[ks][i], acc[i][j], 0, 0, 0);
+          acc[i][j] = Mfma16<T>::mma(o[ks][TM + j], o[ks][i], acc[i][j]);
     }
   };
   if (nstep >= STAGES) wait_all_barrier<(STAGES - 1) * PER>();   // step 0 landed
   else wait_all_barrier<0>();
   read(0, f[0]);
   // step k: products of k from registers `cur`, reads of k+1 into `nxt`
-  auto step = [&](int k, const bf16x8(&cur)[2 * SL][NF], bf16x8(&nxt)[2 * SL][NF]) {
+  auto step = [&](int k, const chunk(&cur)[2 * SL][NF], chunk(&nxt)[2 * SL][NF]) {
     if (k + 1 < nstep) {
       // step k+1 landed (later ones may be in flight) and, past the barrier,
       // every wave's reads of step k are done: its buffer is free

@@ -4,29 +4,23 @@
 namespace cs {
 
 // ------------------------------------------------------------- launchers
-// bf16: direct-to-LDS kernels on 16x16x32 MFMAs (k_gemm_w4, k_gemm_ring), tile
-//       shape chosen per launch (choose_tile), K slices of 64, tile groups of
-//       4 tile-rows; all shapes sum in the same order (bitwise equal
-//       results).  K must be a multiple of 64.
-// fp32: register-staged kernel, 128x128 tiles, 4 waves of 64x64, K slices of 16.
-// Narrow N in fp32 (head GEMM, N = patch_dim): register-staged 128x64 tiles.
-struct GemmCfg {
-  static constexpr int BM = 128, BN = 128, BK = 16, WM = 64, WN = 64, NW = 4, OCC = 1, GM = 1;
-};
-struct GemmCfgNarrow {
-  static constexpr int BM = 128, BN = 64, BK = 16, WM = 32, WN = 64, NW = 4, OCC = 1, GM = 1;
-};
-constexpr int BF16_BK = 64, BF16_GM = 4;
+// Direct-to-LDS kernels on 16x16 MFMAs, tile shape chosen per launch
+// (choose_tile in bf16, F32_64_TILES in fp32), K slices of 128 bytes, tile
+// groups of 4 tile-rows; all shapes of a type sum in the same order (bitwise
+// equal results).  K must be a multiple of a slice.
+template <typename T> constexpr int SLICE_K = 128 / (int)sizeof(T);
+constexpr int GROUP_M = 4;
 
 // ------------------------------------------------------- weight tiling
-// bf16 weights for the direct-load kernels: [N][K] fp32 row-major ->
-// blocks of W_BLOCK_ROWS rows x BF16_BK columns, block (tn, kt) at
-// ((tn * K/BK + kt) * BN * BK) elements; inside a block row r holds its 8
-// chunks of 8 columns with logical chunk c at physical position
-// c ^ gemm_swz(r), the LDS layout of the kernel.  Rows past N are zero.
+// Weights for the direct-load kernels: [N][K] fp32 row-major -> blocks of
+// W_BLOCK_ROWS rows x SLICE_K columns in the compute type, block (tn, kt) at
+// ((tn * K/SLICE_K + kt) * W_BLOCK_ROWS * SLICE_K) elements; inside a block row
+// r holds its 8 chunks of 16 bytes with logical chunk c at physical position
+// c ^ gemm_swz(r), the LDS layout of the kernels.  Rows past N are zero.
+template <typename T>
 __global__ __launch_bounds__(256) void k_tile_weight(const float* __restrict__ src, int N, int K,
-                                                     bf16* __restrict__ dst, long n_chunks) {
-  constexpr int BN = W_BLOCK_ROWS, BK = BF16_BK, CPR = BK / 8;
+                                                     T* __restrict__ dst, long n_chunks) {
+  constexpr int BN = W_BLOCK_ROWS, BK = SLICE_K<T>, CPR = 8, CH = BK / CPR;
   const long q = (long)blockIdx.x * 256 + threadIdx.x;
   if (q >= n_chunks) return;
   const long blk = q / (BN * CPR);
@@ -35,31 +29,21 @@ __global__ __launch_bounds__(256) void k_tile_weight(const float* __restrict__ s
   const int nk = K / BK;
   const int tn = (int)(blk / nk), kt = (int)(blk % nk);
   const int n = tn * BN + r;
-  const int k0 = kt * BK + (p ^ gemm_swz(r)) * 8;
-  bf16x8 v;
+  const int k0 = kt * BK + (p ^ gemm_swz(r)) * CH;
+  typename Mfma16<T>::chunk v;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = n < N ? (bf16)src[(long)n * K + k0 + e] : (bf16)0.0f;
-  *reinterpret_cast<bf16x8*>(dst + q * 8) = v;
+  for (int e = 0; e < CH; ++e) v[e] = n < N ? to_t<T>(src[(long)n * K + k0 + e]) : to_t<T>(0.0f);
+  *reinterpret_cast<typename Mfma16<T>::chunk*>(dst + q * CH) = v;
 }
 
 long gemm_tiled_weight_elems(int N, int K) { return round_up(N, W_BLOCK_ROWS) * (long)K; }
 
-hipError_t gemm_tile_weight(const float* src, int N, int K, bf16* dst, hipStream_t st) {
-  if (N <= 0 || K % BF16_BK != 0) return hipErrorInvalidValue;
-  const long n_chunks = gemm_tiled_weight_elems(N, K) / 8;
-  hipLaunchKernelGGL(k_tile_weight, dim3((unsigned)cdiv(n_chunks, 256)), dim3(256), 0, st, src, N, K, dst,
+template <typename T>
+hipError_t gemm_tile_weight(const float* src, int N, int K, T* dst, hipStream_t st) {
+  if (N <= 0 || K % SLICE_K<T> != 0) return hipErrorInvalidValue;
+  const long n_chunks = gemm_tiled_weight_elems(N, K) / (16 / (long)sizeof(T));
+  hipLaunchKernelGGL(k_tile_weight<T>, dim3((unsigned)cdiv(n_chunks, 256)), dim3(256), 0, st, src, N, K, dst,
                      n_chunks);
-  return hipGetLastError();
-}
-
-template <typename T, class C, class Epi>
-static hipError_t launch_staged(const T* A, long lda, const T* W, long ldw, int M, int N, int K,
-                                Epi epi, hipStream_t st) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  if (K <= 0 || K % C::BK != 0 || N % 4 != 0) return hipErrorInvalidValue;
-  const long tiles = (long)cdiv(M, C::BM) * cdiv(N, C::BN);
-  hipLaunchKernelGGL((k_gemm<T, C::BM, C::BN, C::BK, C::WM, C::WN, C::NW, C::OCC, C::GM, Epi>),
-                     dim3((unsigned)tiles), dim3(64 * C::NW), 0, st, A, lda, W, ldw, M, N, K, epi);
   return hipGetLastError();
 }
 
@@ -107,7 +91,7 @@ constexpr long LARGE_TILES = 512, LARGE_MIN_N = 1024;
 constexpr double LARGE_MARGIN = 0.97;
 
 static Bf16Tile choose_tile(long M, long N, long K, bool residual, bool allow_192) {
-  const double nk = (double)(K / BF16_BK);
+  const double nk = (double)(K / SLICE_K<bf16>);
   auto cost = [&](int i) {
     const TileCost& c = TILE_COST[i];
     const long tiles = (long)cdiv(M, c.bm) * cdiv(N, c.bn), round = 256L * c.slots;
@@ -132,26 +116,30 @@ static Bf16Tile choose_tile(long M, long N, long K, bool residual, bool allow_19
 template <int BM, int BN, int OCC, int PD, class Epi>
 static void launch_w4(const bf16* A, long lda, const bf16* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
   const unsigned tiles = (unsigned)((long)cdiv(M, BM) * cdiv(N, BN));
-  hipLaunchKernelGGL((k_gemm_w4<BM, BN, OCC, BF16_GM, PD, Epi>), dim3(tiles), dim3(256), 0, st, A, lda, W, M, N, K,
+  hipLaunchKernelGGL((k_gemm_w4<BM, BN, OCC, GROUP_M, PD, Epi>), dim3(tiles), dim3(256), 0, st, A, lda, W, M, N, K,
                      epi);
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, class Epi>
-static void launch_ring(const bf16* A, long lda, const bf16* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
+template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, int OCC, class Epi>
+static void launch_ring(const T* A, long lda, const T* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
   const unsigned tiles = (unsigned)((long)cdiv(M, BM) * cdiv(N, BN));
-  hipLaunchKernelGGL((k_gemm_ring<BM, BN, WGM, WGN, STAGES, 2, BF16_GM, Epi>), dim3(tiles), dim3(64 * WGM * WGN), 0,
-                     st, A, lda, W, M, N, K, epi);
+  hipLaunchKernelGGL((k_gemm_ring<T, BM, BN, WGM, WGN, 2, STAGES, OCC, GROUP_M, Epi>), dim3(tiles),
+                     dim3(64 * WGM * WGN), 0, st, A, lda, W, M, N, K, epi);
 }
 
+// fp32: 64 x 64 tiles from six per CU on (768 x 8960 x 1536: 180 us against
+// 183 with 32 x 32, 3000 x 8960 x 1536: 629 against 661, half the loads), below
+// that 32 x 32 (768 x 1536 x 8960, 288 tiles of 64 x 64: 183 against 267 us).
+constexpr long F32_64_TILES = 6 * 256;
+
+// W is in the tiled layout (row stride K).
 template <typename T, class Epi>
-static hipError_t launch(const T* A, long lda, const T* W, long ldw, int M, int N, int K, Epi epi,
-                         hipStream_t st) {
+static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, Epi epi, hipStream_t st) {
+  if (M <= 0 || N <= 0) return hipSuccess;
+  if (K <= 0 || K % SLICE_K<T> != 0 || N % 4 != 0) return hipErrorInvalidValue;
+  // per-tile buffer ranges are 32-bit byte counts
+  if ((long)W_BLOCK_ROWS * std::max(lda, (long)K) * (long)sizeof(T) > 0x7FFFFFFFL) return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 2) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    if (K <= 0 || K % BF16_BK != 0 || N % 4 != 0) return hipErrorInvalidValue;
-    // W is pre-tiled (row stride K); per-tile buffer ranges are 32-bit byte counts
-    if (ldw != K) return hipErrorInvalidValue;
-    if ((long)W_BLOCK_ROWS * std::max(lda, (long)K) * 2 > 0x7FFFFFFFL) return hipErrorInvalidValue;
     constexpr bool RES = EpiIsResidual<Epi>::value, A192 = EpiAllows192<Epi>::value;
     // residual operands in flight per wave: with one wave per SIMD nothing
     // else hides their latency, with two workgroups per CU half as many do
@@ -164,36 +152,39 @@ static hipError_t launch(const T* A, long lda, const T* W, long ldw, int M, int 
       case W4_128x256: launch_w4<128, 256, 1, PD>(A, lda, W, M, N, K, epi, st); break;
       case W4_128x128: launch_w4<128, 128, 2, PD2>(A, lda, W, M, N, K, epi, st); break;
       case W4_64x64: launch_w4<64, 64, 3, 2>(A, lda, W, M, N, K, epi, st); break;
-      case RING_64x64: launch_ring<64, 64, 2, 4, 4>(A, lda, W, M, N, K, epi, st); break;
-      case RING_32x64: launch_ring<32, 64, 1, 4, 3>(A, lda, W, M, N, K, epi, st); break;
-      default: launch_ring<32, 32, 2, 2, 4>(A, lda, W, M, N, K, epi, st);
+      case RING_64x64: launch_ring<T, 64, 64, 2, 4, 4, 2>(A, lda, W, M, N, K, epi, st); break;
+      case RING_32x64: launch_ring<T, 32, 64, 1, 4, 3, 2>(A, lda, W, M, N, K, epi, st); break;
+      default: launch_ring<T, 32, 32, 2, 2, 4, 2>(A, lda, W, M, N, K, epi, st);
     }
-    return hipGetLastError();
   } else {
-    return launch_staged<T, GemmCfg>(A, lda, W, ldw, M, N, K, epi, st);
+    if ((long)cdiv(M, 64) * cdiv(N, 64) >= F32_64_TILES)
+      launch_ring<T, 64, 64, 2, 4, 2, 4>(A, lda, W, M, N, K, epi, st);
+    else
+      launch_ring<T, 32, 32, 2, 2, 2, 4>(A, lda, W, M, N, K, epi, st);
   }
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t gemm_store(const T* A, long lda, const T* W, int M, int N, int K, const float* bias,
                       int act, T* out, long ldo, hipStream_t st) {
   if (!bias) return hipErrorInvalidValue;
-  if (act == 1) return launch<T>(A, lda, W, K, M, N, K, EpiStore<T, 1>{out, ldo, bias}, st);
-  return launch<T>(A, lda, W, K, M, N, K, EpiStore<T, 0>{out, ldo, bias}, st);
+  if (act == 1) return launch<T>(A, lda, W, M, N, K, EpiStore<T, 1>{out, ldo, bias}, st);
+  return launch<T>(A, lda, W, M, N, K, EpiStore<T, 0>{out, ldo, bias}, st);
 }
 
 template <typename T>
 hipError_t gemm_store_t(const T* A, long lda, const T* W, int M, int N, int K, const float* bias,
                         T* out, long ldo, hipStream_t st) {
   EpiStoreT<T> e{out, ldo, bias};
-  return launch<T>(A, lda, W, K, M, N, K, e, st);
+  return launch<T>(A, lda, W, M, N, K, e, st);
 }
 
 template <typename T>
 hipError_t gemm_qkv(const T* A, const T* W, int M, int d, const float* bias, int L, T* qk, T* vt,
                     long vt_ld, hipStream_t st) {
   EpiQKV<T> e{qk, vt, bias, d, L, vt_ld, (long)d * vt_ld};
-  return launch<T>(A, d, W, d, M, 3 * d, d, e, st);
+  return launch<T>(A, d, W, M, 3 * d, d, e, st);
 }
 
 template <typename T>
@@ -201,18 +192,18 @@ hipError_t gemm_residual(const T* A, long lda, const T* W, int M, int N, int K, 
                          const float* gate, float* z, T* y, hipStream_t st) {
   if (!bias) return hipErrorInvalidValue;
   if (y) {
-    if (gate) return launch<T>(A, lda, W, K, M, N, K, EpiResidualStore<1, T>{z, N, bias, gate, y}, st);
-    return launch<T>(A, lda, W, K, M, N, K, EpiResidualStore<0, T>{z, N, bias, nullptr, y}, st);
+    if (gate) return launch<T>(A, lda, W, M, N, K, EpiResidualStore<1, T>{z, N, bias, gate, y}, st);
+    return launch<T>(A, lda, W, M, N, K, EpiResidualStore<0, T>{z, N, bias, nullptr, y}, st);
   }
-  if (gate) return launch<T>(A, lda, W, K, M, N, K, EpiResidual<1>{z, N, bias, gate}, st);
-  return launch<T>(A, lda, W, K, M, N, K, EpiResidual<0>{z, N, bias, nullptr}, st);
+  if (gate) return launch<T>(A, lda, W, M, N, K, EpiResidual<1>{z, N, bias, gate}, st);
+  return launch<T>(A, lda, W, M, N, K, EpiResidual<0>{z, N, bias, nullptr}, st);
 }
 
 template <typename T>
 hipError_t gemm_patch(const T* A, const T* W, int M, int d, int P, const float* bias, float* z,
                       hipStream_t st) {
   EpiPatch e{z, d, bias};
-  return launch<T>(A, P, W, P, M, d, P, e, st);
+  return launch<T>(A, P, W, M, d, P, e, st);
 }
 
 template <typename T>
@@ -220,14 +211,11 @@ hipError_t gemm_head(const T* A, const T* W, int M, int d, int P, const float* b
                      const int* slot_id, int L, int gh, int gw, int F, int H, int Wd, long D,
                      hipStream_t st) {
   EpiHead e{out, slot_id, bias, L, gh, gw, F, H, Wd, D};
-  if constexpr (sizeof(T) == 2) {
-    return launch<T>(A, d, W, d, M, P, d, e, st);
-  } else {
-    return launch_staged<T, GemmCfgNarrow>(A, d, W, d, M, P, d, e, st);
-  }
+  return launch<T>(A, d, W, M, P, d, e, st);
 }
 
 #define CS_INST(T)                                                                              \
+  template hipError_t gemm_tile_weight<T>(const float*, int, int, T*, hipStream_t);             \
   template hipError_t gemm_store<T>(const T*, long, const T*, int, int, int, const float*, int, \
                                     T*, long, hipStream_t);                                     \
   template hipError_t gemm_store_t<T>(const T*, long, const T*, int, int, int, const float*,   \

@@ -591,11 +591,11 @@ static cs_status model_init_impl(const cs_model_desc* desc, const float* weights
   m->Ltp = round_up(desc->text_len, kvt);
 
   // arena: matrices in the compute type, vectors fp32; block modulation
-  // tables gathered into one [n_blocks][6][d] array.  In bf16 the weights of
-  // the direct-load GEMMs (every matrix except the three time-conditioning
-  // GEMV matrices) are stored in their tiled layout.
+  // tables gathered into one [n_blocks][6][d] array.  The weights of the
+  // GEMMs (every matrix except the three time-conditioning GEMV matrices) are
+  // stored in their tiled layout.
   auto tiled = [&](const TSpec& t) {
-    return m->esz == 2 && t.matrix && t.name != "time1_w" && t.name != "time2_w" &&
+    return t.matrix && t.name != "time1_w" && t.name != "time2_w" &&
            t.name != "mod_w";
   };
   std::vector<size_t> off(spec.size());
@@ -625,8 +625,10 @@ static cs_status model_init_impl(const cs_model_desc* desc, const float* weights
       ptr[i] = dst;
       ++table_j;
     } else if (spec[i].matrix) {
-      if (tiled(spec[i]))
-        HIPC(gemm_tile_weight(weights + src, (int)spec[i].rows, (int)spec[i].cols, (bf16*)(base + off[i]), st));
+      if (tiled(spec[i]) && m->esz == 2)
+        HIPC(gemm_tile_weight<bf16>(weights + src, (int)spec[i].rows, (int)spec[i].cols, (bf16*)(base + off[i]), st));
+      else if (tiled(spec[i]))
+        HIPC(gemm_tile_weight<float>(weights + src, (int)spec[i].rows, (int)spec[i].cols, (float*)(base + off[i]), st));
       else if (m->esz == 2)
         HIPC(cast_from_f32<bf16>(weights + src, (bf16*)(base + off[i]), n, st));
       else
