@@ -1,5 +1,5 @@
 // Row-wise and small kernels: layer norm with adaLN modulation, RMSNorm with
-// 3D RoPE, patchify, GEMV for the timestep MLP, modulation tables, casts.
+// 3D RoPE, patchify, time conditioning (GEMVs and modulation tables), casts.
 // All are bandwidth- or latency-bound; one wave per row, reductions in fp32
 // over the row in a fixed lane/step order.
 #include "kernels.hpp"
@@ -288,79 +288,89 @@ hipError_t patchify(const float* x, const int* slot_id, int n_slots, int cand_di
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------- GEMV
-// One wave per output; the input vector (after the optional SiLU) is staged
-// in LDS once per workgroup.
-template <typename T>
-__global__ __launch_bounds__(256) void k_gemv(const T* __restrict__ W, const float* __restrict__ x,
-                                               const float* __restrict__ b, int N, int K, int act,
-                                               float* __restrict__ y) {
-  extern __shared__ float sx[];
-  for (int k = threadIdx.x; k < K; k += 256) {
-    const float v = x[k];
-    sx[k] = act == 1 ? silu(v) : v;
+// ------------------------------------------------------- time conditioning
+// features -> linear, SiLU, linear (embedding e) -> SiLU, linear (6d modulation
+// m) -> per-block tables m + P_j and head table e + P_head, in three launches:
+// each product's epilogue does what follows it.
+//
+// Bound by reading the weights once (mod_w: 28 MB at d = 1536, 315 MB at d =
+// 5120).  A wave takes GEMV_ROWS rows at a time, 16 bytes per lane and row, so
+// that GEMV_ROWS x K/512 loads are in flight; the input vector is shared by the
+// rows and comes from L2.  Measured for the three together (features, products
+// and tables): 58 -> 18 us at d = 1536, 270 -> 83 us at d = 5120 (mod_w at 5.0
+// TB/s), where 2-byte loads of one row per wave and five launches took the
+// former.
+constexpr int GEMV_ROWS = 4, GEMV_WAVES = 4;
+enum TimeStage { TIME_HIDDEN = 0, TIME_EMBED = 1, TIME_MOD = 2 };
+
+// Sinusoidal timestep features [cos(1000 t w_k), sin(1000 t w_k)], w_k =
+// 10000^(-k/half); the angle is formed in double so that the fp32 features are
+// correctly rounded for large 1000*t*w.
+CS_DEV void time_features(float t, int half, float* out) {
+  for (int k = threadIdx.x; k < half; k += 64 * GEMV_WAVES) {
+    const double om = exp(-log(10000.0) * (double)k / (double)half);
+    const double arg = 1000.0 * (double)t * om;
+    out[k] = (float)cos(arg);
+    out[half + k] = (float)sin(arg);
   }
-  __syncthreads();
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
+}
+
+template <typename T, int STAGE>
+__global__ __launch_bounds__(64 * GEMV_WAVES) void k_time_cond(const T* __restrict__ W, const float* __restrict__ b,
+                                                               const float* __restrict__ x, int N, int K,
+                                                               float t, float* __restrict__ act,
+                                                               const float* __restrict__ tables, int n_tables,
+                                                               float* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) float feat[STAGE == TIME_HIDDEN ? 256 : 4];
+  if constexpr (STAGE == TIME_HIDDEN) {
+    time_features(t, K / 2, feat);
+    __syncthreads();
+    x = feat;
+  }
   const int lane = threadIdx.x & 63;
-  if (n >= N) return;
-  const T* wr = W + (long)n * K;
-  float s = 0.0f;
-  for (int k = lane; k < K; k += 64) s += to_f(wr[k]) * sx[k];
-  s = wave_sum(s);
-  if (lane == 0) y[n] = s + (b ? b[n] : 0.0f);
-}
-
-template <typename T>
-hipError_t gemv(const T* W, const float* x, const float* b, int N, int K, int act, float* y,
-                hipStream_t st) {
-  hipLaunchKernelGGL(k_gemv<T>, dim3((unsigned)cdiv(N, 4)), dim3(256), (size_t)K * sizeof(float),
-                     st, W, x, b, N, K, act, y);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------- time features
-__global__ void k_time_features(float t, int half, float* out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= half) return;
-  // frequency 10000^(-k/half); the angle is formed in double so that the
-  // fp32 features are correctly rounded for large 1000*t*w.
-  const double om = exp(-log(10000.0) * (double)k / (double)half);
-  const double arg = 1000.0 * (double)t * om;
-  out[k] = (float)cos(arg);
-  out[half + k] = (float)sin(arg);
-}
-
-hipError_t time_features(float t, int freq_dim, float* out, hipStream_t st) {
-  const int half = freq_dim / 2;
-  hipLaunchKernelGGL(k_time_features, dim3((unsigned)cdiv(half, 128)), dim3(128), 0, st, t, half,
-                     out);
-  return hipGetLastError();
-}
-
-// --------------------------------------------------------- modulation tables
-__global__ void k_build_mods(const float* __restrict__ m, const float* __restrict__ e,
-                             const float* __restrict__ tables0, long stride, int n_blocks,
-                             const float* __restrict__ head_table, int d, float* __restrict__ mods,
-                             float* __restrict__ hmod) {
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  const long per = 6L * d;
-  if (idx < per * n_blocks) {
-    const int j = (int)(idx / per);
-    const long r = idx - (long)j * per;
-    mods[idx] = m[r] + tables0[(long)j * stride + r];
-  } else if (idx < per * n_blocks + 2L * d) {
-    const long r = idx - per * n_blocks;
-    hmod[r] = e[r % d] + head_table[r];
+  const int n0 = (blockIdx.x * GEMV_WAVES + (threadIdx.x >> 6)) * GEMV_ROWS;
+  if (n0 >= N) return;
+  const T* wr = W + (long)n0 * K;
+  float s[GEMV_ROWS] = {};
+  for (int k = lane * 8; k < K; k += 512) {
+    float xv[8];
+    Vec8<float>::get(x + k, xv);
+#pragma unroll
+    for (int r = 0; r < GEMV_ROWS; ++r) {
+      float wv[8];
+      Vec8<T>::get(wr + (long)r * K + k, wv);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s[r] += wv[i] * xv[i];
+    }
+  }
+  const float4 bv = *reinterpret_cast<const float4*>(b + n0);
+  const float4 y = make_float4(wave_sum(s[0]) + bv.x, wave_sum(s[1]) + bv.y, wave_sum(s[2]) + bv.z,
+                               wave_sum(s[3]) + bv.w);
+  if constexpr (STAGE != TIME_MOD) {
+    if (lane == 0)
+      *reinterpret_cast<float4*>(act + n0) = make_float4(silu(y.x), silu(y.y), silu(y.z), silu(y.w));
+  }
+  if constexpr (STAGE != TIME_HIDDEN) {
+    for (int j = lane; j < n_tables; j += 64) {
+      const float4 p = *reinterpret_cast<const float4*>(tables + (long)j * N + n0);
+      *reinterpret_cast<float4*>(out + (long)j * N + n0) = make_float4(y.x + p.x, y.y + p.y, y.z + p.z, y.w + p.w);
+    }
   }
 }
 
-hipError_t build_mods_strided(const float* m, const float* e, const float* tables0,
-                              long table_stride, int n_blocks, const float* head_table, int d,
-                              float* mods, float* hmod, hipStream_t st) {
-  const long n = 6L * d * n_blocks + 2L * d;
-  hipLaunchKernelGGL(k_build_mods, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, m, e, tables0,
-                     table_stride, n_blocks, head_table, d, mods, hmod);
+template <typename T>
+hipError_t time_conditioning(const TimeCond<T>& c, float t, hipStream_t st) {
+  const int d = c.d;
+  // 16-byte accesses along rows and outputs; the features fill 256 floats
+  if (d % 8 != 0 || c.freq_dim != 256) return hipErrorInvalidValue;
+  auto grid = [](int n) { return dim3((unsigned)cdiv(n, GEMV_ROWS * GEMV_WAVES)); };
+  const dim3 block(64 * GEMV_WAVES);
+  hipLaunchKernelGGL((k_time_cond<T, TIME_HIDDEN>), grid(d), block, 0, st, c.w1, c.b1, (const float*)nullptr, d,
+                     c.freq_dim, t, c.h1, (const float*)nullptr, 0, (float*)nullptr);
+  hipLaunchKernelGGL((k_time_cond<T, TIME_EMBED>), grid(d), block, 0, st, c.w2, c.b2, (const float*)c.h1, d, d, t,
+                     c.e, c.head_table, 2, c.hmod);
+  hipLaunchKernelGGL((k_time_cond<T, TIME_MOD>), grid(6 * d), block, 0, st, c.mod_w, c.mod_b, (const float*)c.e,
+                     6 * d, d, t, (float*)nullptr, c.tables, c.n_blocks, c.mods);
   return hipGetLastError();
 }
 
@@ -419,8 +429,7 @@ template <typename T> hipError_t cast_from_f32(const float* src, T* dst, long n,
                                       const float2*, int, int, hipStream_t);                    \
   template hipError_t patchify<T>(const float*, const int*, int, int, long, int, int, int, int, \
                                   T*, hipStream_t);                                             \
-  template hipError_t gemv<T>(const T*, const float*, const float*, int, int, int, float*,     \
-                              hipStream_t);                                                     \
+  template hipError_t time_conditioning<T>(const TimeCond<T>&, float, hipStream_t);             \
   template hipError_t cast_from_f32<T>(const float*, T*, long, hipStream_t);                 \
   template hipError_t residual_add<T>(float*, const T*, const float*, long, int, hipStream_t);
 CS_INST(bf16)

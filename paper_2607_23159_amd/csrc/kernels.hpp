@@ -65,17 +65,17 @@ hipError_t rmsnorm_rope(T* x, long rows, long ld, int d, int parts, const float*
 template <typename T>
 hipError_t patchify(const float* x, const int* slot_id, int n_slots, int cand_div, long D, int C,
                     int F, int H, int Wd, T* out, hipStream_t st);
-// y[n] = sum_k W[n][k] * act(x[k]) + b[n]  (act: 0 none, 1 SiLU); fp32 out.
-template <typename T>
-hipError_t gemv(const T* W, const float* x, const float* b, int N, int K, int act, float* y,
-                hipStream_t st);
-// Sinusoidal timestep features [cos(1000 t w_k), sin(1000 t w_k)].
-hipError_t time_features(float t, int freq_dim, float* out, hipStream_t st);
-// mods[j][6][d] = m[6d] + table_j (tables at tables0 + j*table_stride);
-// hmod[2][d] = e[d] + head_table.
-hipError_t build_mods_strided(const float* m, const float* e, const float* tables0,
-                              long table_stride, int n_blocks, const float* head_table, int d,
-                              float* mods, float* hmod, hipStream_t st);
+// Time conditioning of timestep t: with s the 256 sinusoidal features of t,
+//   h1 = SiLU(w1 s + b1), e = w2 h1 + b2, m = mod_w SiLU(e) + mod_b,
+//   hmod[2][d] = e + head_table, mods[j][6][d] = m + tables[j].
+// h1 and e are work arrays of d floats (e receives SiLU(e)).
+template <typename T> struct TimeCond {
+  const T *w1, *w2, *mod_w;
+  const float *b1, *b2, *mod_b, *head_table, *tables;
+  int d, freq_dim, n_blocks;
+  float *h1, *e, *hmod, *mods;
+};
+template <typename T> hipError_t time_conditioning(const TimeCond<T>& c, float t, hipStream_t st);
 template <typename T> hipError_t cast_from_f32(const float* src, T* dst, long n, hipStream_t st);
 // z[rows][d] += gate * y (gate: [d] or NULL for 1); d % 8 == 0.  Applies a
 // stored attention-branch output y [rows][d] of the compute type.

@@ -246,8 +246,8 @@ struct cs_model {
   const float* mod_tables = nullptr;  // [n_blocks][6][d]
   std::vector<Block> blocks;
   float2* rope = nullptr;
-  float* cond = nullptr;   // time features, h1, e, m, mods, hmod
-  float *tfeat, *h1, *e, *m, *mods, *hmod;
+  float* cond = nullptr;   // h1, e, mods, hmod
+  float *h1, *e, *mods, *hmod;
   Profiler prof;
   Workspace vel_ws;
   CtxKV vel_ctx;
@@ -375,19 +375,14 @@ static cs_status build_ctx(cs_model* m, CtxKV& c, int b, const float* ctx) {
   return CS_OK;
 }
 
-// Time conditioning for timestep t: e, m, per-block modulation, head modulation.
+// Time conditioning for timestep t: per-block and head modulation.
 template <typename T>
 static cs_status time_cond(cs_model* m, float t) {
-  const cs_model_desc& g = m->desc;
-  hipStream_t st = m->stream;
-  const int d = (int)m->d;
-  ProfScope ps(m->prof, CS_K_OTHER, st);
-  HIPC(time_features(t, g.freq_dim, m->tfeat, st));
-  HIPC(gemv<T>((const T*)m->time1_w, m->tfeat, m->time1_b, d, g.freq_dim, 0, m->h1, st));
-  HIPC(gemv<T>((const T*)m->time2_w, m->h1, m->time2_b, d, d, 1, m->e, st));
-  HIPC(gemv<T>((const T*)m->mod_w, m->e, m->mod_b, 6 * d, d, 1, m->m, st));
-  HIPC(build_mods_strided(m->m, m->e, m->mod_tables, 6L * d, g.n_blocks, m->head_mod, d, m->mods,
-                          m->hmod, st));
+  ProfScope ps(m->prof, CS_K_OTHER, m->stream);
+  const TimeCond<T> c = {(const T*)m->time1_w, (const T*)m->time2_w, (const T*)m->mod_w, m->time1_b, m->time2_b,
+                         m->mod_b, m->head_mod, m->mod_tables, (int)m->d, m->desc.freq_dim, m->desc.n_blocks,
+                         m->h1, m->e, m->hmod, m->mods};
+  HIPC(time_conditioning<T>(c, t, m->stream));
   return CS_OK;
 }
 
@@ -688,13 +683,11 @@ static cs_status model_init_impl(const cs_model_desc* desc, const float* weights
   }
   {
     const long d = m->d;
-    const size_t nf = 256 + d + d + 6 * d + (size_t)desc->n_blocks * 6 * d + 2 * d;
+    const size_t nf = d + d + (size_t)desc->n_blocks * 6 * d + 2 * d;
     TRY(dmalloc((void**)&m->cond, nf * sizeof(float)));
-    m->tfeat = m->cond;
-    m->h1 = m->tfeat + 256;
+    m->h1 = m->cond;
     m->e = m->h1 + d;
-    m->m = m->e + d;
-    m->mods = m->m + 6 * d;
+    m->mods = m->e + d;
     m->hmod = m->mods + (long)desc->n_blocks * 6 * d;
   }
   HIPC(hipStreamSynchronize(st));
