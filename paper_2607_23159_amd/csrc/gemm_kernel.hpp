@@ -113,6 +113,10 @@ CS_DEV void gemm_epilogue16_deep(const f32x4 (&acc)[TM][TN], int row_base, int c
 // ---------------------------------------------------------------------------
 constexpr int W_BLOCK_ROWS = 256;   // rows of a block of the tiled weights
 
+// Batched launches (blockIdx.y = item): the same A against n weight matrices
+// w_stride elements apart, with an epilogue that moves to item z (Epi::item).
+template <class Epi> struct EpiBatched : std::false_type {};
+
 // Tile order: the launch is split into 8 contiguous ranges, one per XCD
 // (workgroups are dealt round-robin to the 8 dies).  Inside a range, tiles are
 // visited in groups of GM tile-rows, column-major within the group, so the
@@ -176,7 +180,11 @@ CS_DEV void mfma_16x16x32_agpr(f32x4& acc, const bf16x8& a, const bf16x8& b) {
 template <int BM, int BN, int OCC, int GM, int PD, class Epi>
 __global__ __launch_bounds__(256, OCC) void k_gemm_w4(const bf16* __restrict__ A, long lda,
                                                     const bf16* __restrict__ W, int M, int N,
-                                                    int K, Epi epi) {
+                                                    int K, long w_stride, Epi epi) {
+  if constexpr (EpiBatched<Epi>::value) {
+    W += blockIdx.y * w_stride;
+    epi.item(blockIdx.y);
+  }
   constexpr int BK = 64, NWAVE = 4, WM = BM / 2, WN = BN / 2;
   constexpr int CH = 8;                       // bf16 per 16-byte chunk
   constexpr int CPR = BK / CH;                // chunks per LDS row
@@ -387,7 +395,11 @@ template <> struct Mfma16<float> {
 template <typename T, int BM, int BN, int WGM, int WGN, int SL, int STAGES, int OCC, int GM, class Epi>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __restrict__ A, long lda,
                                                                   const T* __restrict__ W, int M,
-                                                                  int N, int K, Epi epi) {
+                                                                  int N, int K, long w_stride, Epi epi) {
+  if constexpr (EpiBatched<Epi>::value) {
+    W += blockIdx.y * w_stride;
+    epi.item(blockIdx.y);
+  }
   typedef typename Mfma16<T>::chunk chunk;
   constexpr int ES = (int)sizeof(T), CH = 16 / ES, BK = 8 * CH, RPI = 8, NWAVE = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16, NF = TM + TN;
@@ -566,7 +578,8 @@ struct GeluF { CS_DEV float operator()(float x) const { return gelu_tanh(x); } }
 // 1.895 ms, FFN up + GELU (N = 8960) unchanged (5.877 vs 5.886 ms); same
 // values.
 template <typename T, int ACT> struct EpiStore {  // ACT: 0 none, 1 tanh-GELU
-  T* out; long ldo; const float* bias;
+  T* out; long ldo; const float* bias; long out_stride = 0, bias_stride = 0;
+  CS_DEV void item(int z) { out += z * out_stride; bias += z * bias_stride; }
   typedef NoPre Pre;
   CS_DEV Pre pre(int, int) const { return {}; }
   CS_DEV void operator()(int row, int col0, const float* v, const Pre&) const {
@@ -590,6 +603,7 @@ template <typename T, int ACT> struct EpiStore {  // ACT: 0 none, 1 tanh-GELU
   }
 };
 template <int ACT> struct EpiStagesTiles<EpiStore<bf16, ACT>> : std::true_type {};
+template <typename T> struct EpiBatched<EpiStore<T, 0>> : std::true_type {};
 
 // Self-attention projection: columns [0, 2d) are q and k, stored row-major
 // [row][2d]; columns [2d, 3d) are v, stored transposed per stream as
@@ -679,7 +693,8 @@ template <> struct EpiStagesTiles<EpiQKV<bf16>> : std::true_type {};
 
 // Transposed store of a single-stream projection: out[col][row].
 template <typename T> struct EpiStoreT {
-  T* out; long ldo; const float* bias;
+  T* out; long ldo; const float* bias; long out_stride = 0, bias_stride = 0;
+  CS_DEV void item(int z) { out += z * out_stride; bias += z * bias_stride; }
   typedef NoPre Pre;
   CS_DEV Pre pre(int, int) const { return {}; }
   CS_DEV void operator()(int row, int col0, const float* v, const Pre&) const {
@@ -687,6 +702,8 @@ template <typename T> struct EpiStoreT {
     for (int r = 0; r < 4; ++r) out[(long)(col0 + r) * ldo + row] = to_t<T>(v[r]);
   }
 };
+
+template <typename T> struct EpiBatched<EpiStoreT<T>> : std::true_type {};
 
 // Residual update z += gate * (acc + bias) (GATED = 0: gate 1).  The
 // updated residual is stored non-temporally: it is read again only by the

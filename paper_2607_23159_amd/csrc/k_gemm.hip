@@ -90,17 +90,17 @@ static const TileCost TILE_COST[N_TILES] = {
 constexpr long LARGE_TILES = 512, LARGE_MIN_N = 1024;
 constexpr double LARGE_MARGIN = 0.97;
 
-static Bf16Tile choose_tile(long M, long N, long K, bool residual, bool allow_192) {
+static Bf16Tile choose_tile(long M, long N, long K, long batch, bool residual, bool allow_192) {
   const double nk = (double)(K / SLICE_K<bf16>);
   auto cost = [&](int i) {
     const TileCost& c = TILE_COST[i];
-    const long tiles = (long)cdiv(M, c.bm) * cdiv(N, c.bn), round = 256L * c.slots;
+    const long tiles = (long)cdiv(M, c.bm) * cdiv(N, c.bn) * batch, round = 256L * c.slots;
     const double epi = c.epi + (residual ? c.epi_res : 0.0), r = (double)(tiles % round) / (double)round;
     double t = c.fixed + (double)(tiles / round) * (nk * c.full + epi);
     if (r > 0) t += nk * (c.lone + (c.full - c.lone) * r) + epi * 0.5 * (1.0 + r);
     return t;
   };
-  const long tiles256 = (long)cdiv(M, 256) * cdiv(N, 256);
+  const long tiles256 = (long)cdiv(M, 256) * cdiv(N, 256) * batch;
   if (tiles256 >= LARGE_TILES && N >= LARGE_MIN_N)
     return allow_192 && cost(W4_192x256) < LARGE_MARGIN * cost(W4_256x256) ? W4_192x256 : W4_256x256;
   int best = W4_256x256;
@@ -113,18 +113,22 @@ static Bf16Tile choose_tile(long M, long N, long K, bool residual, bool allow_19
   return (Bf16Tile)best;
 }
 
+struct GemmBatch { int n; long w_stride; };
+
 template <int BM, int BN, int OCC, int PD, class Epi>
-static void launch_w4(const bf16* A, long lda, const bf16* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
+static void launch_w4(const bf16* A, long lda, const bf16* W, int M, int N, int K, GemmBatch b, const Epi& epi,
+                      hipStream_t st) {
   const unsigned tiles = (unsigned)((long)cdiv(M, BM) * cdiv(N, BN));
-  hipLaunchKernelGGL((k_gemm_w4<BM, BN, OCC, GROUP_M, PD, Epi>), dim3(tiles), dim3(256), 0, st, A, lda, W, M, N, K,
-                     epi);
+  hipLaunchKernelGGL((k_gemm_w4<BM, BN, OCC, GROUP_M, PD, Epi>), dim3(tiles, (unsigned)b.n), dim3(256), 0, st, A, lda,
+                     W, M, N, K, b.w_stride, epi);
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, int OCC, class Epi>
-static void launch_ring(const T* A, long lda, const T* W, int M, int N, int K, const Epi& epi, hipStream_t st) {
+static void launch_ring(const T* A, long lda, const T* W, int M, int N, int K, GemmBatch b, const Epi& epi,
+                        hipStream_t st) {
   const unsigned tiles = (unsigned)((long)cdiv(M, BM) * cdiv(N, BN));
-  hipLaunchKernelGGL((k_gemm_ring<T, BM, BN, WGM, WGN, 2, STAGES, OCC, GROUP_M, Epi>), dim3(tiles),
-                     dim3(64 * WGM * WGN), 0, st, A, lda, W, M, N, K, epi);
+  hipLaunchKernelGGL((k_gemm_ring<T, BM, BN, WGM, WGN, 2, STAGES, OCC, GROUP_M, Epi>), dim3(tiles, (unsigned)b.n),
+                     dim3(64 * WGM * WGN), 0, st, A, lda, W, M, N, K, b.w_stride, epi);
 }
 
 // fp32: 64 x 64 tiles from six per CU on (768 x 8960 x 1536: 180 us against
@@ -134,8 +138,10 @@ constexpr long F32_64_TILES = 6 * 256;
 
 // W is in the tiled layout (row stride K).
 template <typename T, class Epi>
-static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, Epi epi, hipStream_t st) {
+static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, Epi epi, hipStream_t st,
+                         GemmBatch b = {1, 0}) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  if (b.n < 1 || b.n > MAX_BATCH || (b.n > 1 && !EpiBatched<Epi>::value)) return hipErrorInvalidValue;
   if (K <= 0 || K % SLICE_K<T> != 0 || N % 4 != 0) return hipErrorInvalidValue;
   // per-tile buffer ranges are 32-bit byte counts
   if ((long)W_BLOCK_ROWS * std::max(lda, (long)K) * (long)sizeof(T) > 0x7FFFFFFFL) return hipErrorInvalidValue;
@@ -144,23 +150,23 @@ static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, 
     // residual operands in flight per wave: with one wave per SIMD nothing
     // else hides their latency, with two workgroups per CU half as many do
     constexpr int PD = RES ? 8 : 2, PD2 = RES ? 4 : 2;
-    switch (choose_tile(M, N, K, RES, A192)) {
-      case W4_256x256: launch_w4<256, 256, 1, PD>(A, lda, W, M, N, K, epi, st); break;
+    switch (choose_tile(M, N, K, b.n, RES, A192)) {
+      case W4_256x256: launch_w4<256, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
       case W4_192x256:
-        if constexpr (A192) launch_w4<192, 256, 1, PD>(A, lda, W, M, N, K, epi, st);
+        if constexpr (A192) launch_w4<192, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st);
         break;
-      case W4_128x256: launch_w4<128, 256, 1, PD>(A, lda, W, M, N, K, epi, st); break;
-      case W4_128x128: launch_w4<128, 128, 2, PD2>(A, lda, W, M, N, K, epi, st); break;
-      case W4_64x64: launch_w4<64, 64, 3, 2>(A, lda, W, M, N, K, epi, st); break;
-      case RING_64x64: launch_ring<T, 64, 64, 2, 4, 4, 2>(A, lda, W, M, N, K, epi, st); break;
-      case RING_32x64: launch_ring<T, 32, 64, 1, 4, 3, 2>(A, lda, W, M, N, K, epi, st); break;
-      default: launch_ring<T, 32, 32, 2, 2, 4, 2>(A, lda, W, M, N, K, epi, st);
+      case W4_128x256: launch_w4<128, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
+      case W4_128x128: launch_w4<128, 128, 2, PD2>(A, lda, W, M, N, K, b, epi, st); break;
+      case W4_64x64: launch_w4<64, 64, 3, 2>(A, lda, W, M, N, K, b, epi, st); break;
+      case RING_64x64: launch_ring<T, 64, 64, 2, 4, 4, 2>(A, lda, W, M, N, K, b, epi, st); break;
+      case RING_32x64: launch_ring<T, 32, 64, 1, 4, 3, 2>(A, lda, W, M, N, K, b, epi, st); break;
+      default: launch_ring<T, 32, 32, 2, 2, 4, 2>(A, lda, W, M, N, K, b, epi, st);
     }
   } else {
-    if ((long)cdiv(M, 64) * cdiv(N, 64) >= F32_64_TILES)
-      launch_ring<T, 64, 64, 2, 4, 2, 4>(A, lda, W, M, N, K, epi, st);
+    if ((long)cdiv(M, 64) * cdiv(N, 64) * b.n >= F32_64_TILES)
+      launch_ring<T, 64, 64, 2, 4, 2, 4>(A, lda, W, M, N, K, b, epi, st);
     else
-      launch_ring<T, 32, 32, 2, 2, 2, 4>(A, lda, W, M, N, K, epi, st);
+      launch_ring<T, 32, 32, 2, 2, 2, 4>(A, lda, W, M, N, K, b, epi, st);
   }
   return hipGetLastError();
 }
@@ -174,10 +180,19 @@ hipError_t gemm_store(const T* A, long lda, const T* W, int M, int N, int K, con
 }
 
 template <typename T>
-hipError_t gemm_store_t(const T* A, long lda, const T* W, int M, int N, int K, const float* bias,
-                        T* out, long ldo, hipStream_t st) {
-  EpiStoreT<T> e{out, ldo, bias};
-  return launch<T>(A, lda, W, M, N, K, e, st);
+hipError_t gemm_store_batch(const T* A, long lda, const T* W, long w_stride, int n, int M, int N, int K,
+                            const float* bias, long bias_stride, T* out, long ldo, long out_stride,
+                            hipStream_t st) {
+  if (!bias) return hipErrorInvalidValue;
+  return launch<T>(A, lda, W, M, N, K, EpiStore<T, 0>{out, ldo, bias, out_stride, bias_stride}, st, {n, w_stride});
+}
+
+template <typename T>
+hipError_t gemm_store_t_batch(const T* A, long lda, const T* W, long w_stride, int n, int M, int N, int K,
+                              const float* bias, long bias_stride, T* out, long ldo, long out_stride,
+                              hipStream_t st) {
+  if (!bias) return hipErrorInvalidValue;
+  return launch<T>(A, lda, W, M, N, K, EpiStoreT<T>{out, ldo, bias, out_stride, bias_stride}, st, {n, w_stride});
 }
 
 template <typename T>
@@ -218,8 +233,10 @@ hipError_t gemm_head(const T* A, const T* W, int M, int d, int P, const float* b
   template hipError_t gemm_tile_weight<T>(const float*, int, int, T*, hipStream_t);             \
   template hipError_t gemm_store<T>(const T*, long, const T*, int, int, int, const float*, int, \
                                     T*, long, hipStream_t);                                     \
-  template hipError_t gemm_store_t<T>(const T*, long, const T*, int, int, int, const float*,   \
-                                      T*, long, hipStream_t);                                   \
+  template hipError_t gemm_store_batch<T>(const T*, long, const T*, long, int, int, int, int,   \
+                                          const float*, long, T*, long, long, hipStream_t);     \
+  template hipError_t gemm_store_t_batch<T>(const T*, long, const T*, long, int, int, int, int, \
+                                            const float*, long, T*, long, long, hipStream_t);   \
   template hipError_t gemm_qkv<T>(const T*, const T*, int, int, const float*, int, T*, T*,     \
                                   long, hipStream_t);                                           \
   template hipError_t gemm_residual<T>(const T*, long, const T*, int, int, int, const float*,  \

@@ -121,14 +121,14 @@ __global__ __launch_bounds__(256) void k_rmsnorm_rope(T* __restrict__ x, long ro
                                                        int parts, const float* __restrict__ g0,
                                                        const float* __restrict__ g1,
                                                        const float2* __restrict__ rope, int L,
-                                                       int head_dim) {
+                                                       int head_dim, NormGroups gr) {
   const long item = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (item >= rows * parts) return;
   const long row = item / parts;
   const int part = (int)(item - row * parts);
-  T* xr = x + row * ld + (long)part * d;
-  const float* g = part == 0 ? g0 : g1;
+  T* xr = x + blockIdx.y * gr.x + row * ld + (long)part * d;
+  const float* g = (part == 0 ? g0 : g1) + blockIdx.y * gr.g;
   const int npair = d >> 1;
   float s = 0.0f;
   for (int p = lane; p < npair; p += 64) {
@@ -187,14 +187,14 @@ __global__ __launch_bounds__(256) void k_rmsnorm_rope_reg(T* __restrict__ x, lon
                                                            const float* __restrict__ g0,
                                                            const float* __restrict__ g1,
                                                            const float2* __restrict__ rope, int L,
-                                                           int head_dim) {
+                                                           int head_dim, NormGroups gr) {
   const long item = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (item >= rows * parts) return;
   const long row = item / parts;
   const int part = (int)(item - row * parts);
-  T* xr = x + row * ld + (long)part * d;
-  const float* g = part == 0 ? g0 : g1;
+  T* xr = x + blockIdx.y * gr.x + row * ld + (long)part * d;
+  const float* g = (part == 0 ? g0 : g1) + blockIdx.y * gr.g;
   float v[NV][8];
 #pragma unroll
   for (int k = 0; k < NV; ++k) Vec8<T>::get(xr + 8 * (k * 64 + lane), v[k]);
@@ -232,20 +232,22 @@ __global__ __launch_bounds__(256) void k_rmsnorm_rope_reg(T* __restrict__ x, lon
 
 template <typename T>
 hipError_t rmsnorm_rope(T* x, long rows, long ld, int d, int parts, const float* g0,
-                        const float* g1, const float2* rope, int L, int head_dim, hipStream_t st) {
+                        const float* g1, const float2* rope, int L, int head_dim, hipStream_t st,
+                        NormGroups gr) {
   if (rows <= 0) return hipSuccess;
-  const dim3 grid((unsigned)cdiv(rows * parts, 4)), block(256);
+  if (gr.n < 1 || gr.n > MAX_BATCH) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)cdiv(rows * parts, 4), (unsigned)gr.n), block(256);
   switch (d % 512 == 0 ? d / 512 : 0) {
 #define CS_RR(NV)                                                                                \
   case NV:                                                                                       \
     hipLaunchKernelGGL((k_rmsnorm_rope_reg<T, NV>), grid, block, 0, st, x, rows, ld, d, parts, g0, \
-                       g1, rope, L, head_dim);                                                   \
+                       g1, rope, L, head_dim, gr);                                               \
     break;
     CS_RR(1) CS_RR(2) CS_RR(3) CS_RR(4) CS_RR(6) CS_RR(8) CS_RR(10) CS_RR(12)
 #undef CS_RR
     default:
       hipLaunchKernelGGL(k_rmsnorm_rope<T>, grid, block, 0, st, x, rows, ld, d, parts, g0, g1, rope,
-                         L, head_dim);
+                         L, head_dim, gr);
   }
   return hipGetLastError();
 }
@@ -410,15 +412,26 @@ hipError_t residual_add(float* z, const T* y, const float* gate, long rows, int 
 }
 
 // ------------------------------------------------------------------- casts
-template <typename T>
-__global__ void k_cast(const float* __restrict__ s, T* __restrict__ d, long n) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) d[i] = to_t<T>(s[i]);
+// 8 elements per thread where source and destination allow 16-byte accesses
+// (512 x 4096 text rows: 9.7 -> 6.3 us), else one.
+template <typename T, int V>
+__global__ __launch_bounds__(256) void k_cast(const float* __restrict__ s, T* __restrict__ d, long n) {
+  const long i = ((long)blockIdx.x * 256 + threadIdx.x) * V;
+  if (V == 8 && i + V <= n) {
+    float f[8];
+    Vec8<float>::get(s + i, f);
+    Vec8<T>::put(d + i, f);
+  } else {
+    for (long k = i; k < n && k < i + V; ++k) d[k] = to_t<T>(s[k]);
+  }
 }
 
 template <typename T> hipError_t cast_from_f32(const float* src, T* dst, long n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cast<T>, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, src, dst, n);
+  if ((((uintptr_t)src | (uintptr_t)dst) & 15) == 0)
+    hipLaunchKernelGGL((k_cast<T, 8>), dim3((unsigned)cdiv(n, 256 * 8)), dim3(256), 0, st, src, dst, n);
+  else
+    hipLaunchKernelGGL((k_cast<T, 1>), dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, src, dst, n);
   return hipGetLastError();
 }
 
@@ -426,7 +439,7 @@ template <typename T> hipError_t cast_from_f32(const float* src, T* dst, long n,
   template hipError_t layer_norm_mod<T>(const float*, long, int, const float*, const float*,   \
                                         int, T*, hipStream_t);                                  \
   template hipError_t rmsnorm_rope<T>(T*, long, long, int, int, const float*, const float*,    \
-                                      const float2*, int, int, hipStream_t);                    \
+                                      const float2*, int, int, hipStream_t, NormGroups);        \
   template hipError_t patchify<T>(const float*, const int*, int, int, long, int, int, int, int, \
                                   T*, hipStream_t);                                             \
   template hipError_t time_conditioning<T>(const TimeCond<T>&, float, hipStream_t);             \

@@ -5,6 +5,9 @@
 
 namespace cs {
 
+// Items of one batched launch (the grid's second dimension).
+constexpr int MAX_BATCH = 65535;
+
 // ---- GEMM (k_gemm.hip).  W is [N][K] (K contiguous); every variant adds a
 // bias vector (non-NULL) in its epilogue.  W is stored in the tiled layout of
 // gemm_tile_weight, in the compute type.
@@ -14,9 +17,17 @@ hipError_t gemm_tile_weight(const float* src, int N, int K, T* dst, hipStream_t 
 template <typename T>
 hipError_t gemm_store(const T* A, long lda, const T* W, int M, int N, int K, const float* bias,
                       int act, T* out, long ldo, hipStream_t st);
+// n (at most MAX_BATCH) products of the same A with weight matrices w_stride elements apart (biases
+// bias_stride, outputs out_stride apart): out_z[M][N], or transposed
+// out_z[N][ldo].
 template <typename T>
-hipError_t gemm_store_t(const T* A, long lda, const T* W, int M, int N, int K, const float* bias,
-                        T* out, long ldo, hipStream_t st);
+hipError_t gemm_store_batch(const T* A, long lda, const T* W, long w_stride, int n, int M, int N, int K,
+                            const float* bias, long bias_stride, T* out, long ldo, long out_stride,
+                            hipStream_t st);
+template <typename T>
+hipError_t gemm_store_t_batch(const T* A, long lda, const T* W, long w_stride, int n, int M, int N, int K,
+                              const float* bias, long bias_stride, T* out, long ldo, long out_stride,
+                              hipStream_t st);
 template <typename T>
 hipError_t gemm_qkv(const T* A, const T* W, int M, int d, const float* bias, int L, T* qk, T* vt,
                     long vt_ld, hipStream_t st);
@@ -56,11 +67,13 @@ hipError_t layer_norm_mod(const float* z, long rows, int d, const float* shift_o
 // In-place RMSNorm (gain) over the first d columns of each row of x (row
 // stride ld, `parts` consecutive d-wide parts per row, each its own norm),
 // then optional 3D RoPE per head with table rope[token][head_dim/2]
-// (cos, sin), token = row % L.
+// (cos, sin), token = row % L.  groups.n > 1: the same for n arrays of `rows`
+// rows, groups.x and their gains groups.g elements apart.
+struct NormGroups { int n; long x, g; };
 template <typename T>
 hipError_t rmsnorm_rope(T* x, long rows, long ld, int d, int parts, const float* gain0,
                         const float* gain1, const float2* rope, int L, int head_dim,
-                        hipStream_t st);
+                        hipStream_t st, NormGroups groups = {1, 0, 0});
 // Patchify latents of the listed streams into rows [slot*L + tok][C*4].
 template <typename T>
 hipError_t patchify(const float* x, const int* slot_id, int n_slots, int cand_div, long D, int C,

@@ -364,13 +364,26 @@ static cs_status build_ctx(cs_model* m, CtxKV& c, int b, const float* ctx) {
   HIPC(gemm_store<T>(tmp0, g.text_dim, (const T*)m->text1_w, (int)Lt, (int)d, g.text_dim,
                      m->text1_b, 1, tmp1, d, st));
   HIPC(gemm_store<T>(tmp1, d, (const T*)m->text2_w, (int)Lt, (int)d, (int)d, m->text2_b, 0, emb, d, st));
-  for (int j = 0; j < g.n_blocks; ++j) {
-    const Block& bk = m->blocks[j];
-    T* K = (T*)c.k + ((long)j * c.B + b) * Lt * d;
-    T* VT = (T*)c.vt + ((long)j * c.B + b) * d * m->Ltp;
-    HIPC(gemm_store<T>(emb, d, (const T*)bk.cak_w, (int)Lt, (int)d, (int)d, bk.cak_b, 0, K, d, st));
-    HIPC(rmsnorm_rope<T>(K, Lt, d, (int)d, 1, bk.cak_gain, nullptr, nullptr, 1, g.head_dim, st));
-    HIPC(gemm_store_t<T>(emb, d, (const T*)bk.cav_w, (int)Lt, (int)d, (int)d, bk.cav_b, VT, m->Ltp, st));
+  // Keys and values of all blocks: one batched product each and one norm pass
+  // (a block's product alone is 96 to 288 small tiles: 30 blocks of the 1.3B
+  // shape took 0.28 ms of 9.4 us launches for the keys, one launch takes 0.10
+  // ms, the values likewise).  Every block lays its weights out alike, so items
+  // are a constant stride apart.
+  const Block& b0 = m->blocks[0];
+  const Block& b1 = m->blocks[g.n_blocks > 1 ? 1 : 0];
+  const long wk = (const T*)b1.cak_w - (const T*)b0.cak_w, wv = (const T*)b1.cav_w - (const T*)b0.cav_w;
+  T* K = (T*)c.k + (long)b * Lt * d;
+  T* VT = (T*)c.vt + (long)b * d * m->Ltp;
+  const long ks = (long)c.B * Lt * d, vs = (long)c.B * d * m->Ltp;
+  const long bk = b1.cak_b - b0.cak_b, bv = b1.cav_b - b0.cav_b, gk = b1.cak_gain - b0.cak_gain;
+  for (long j = 0; j < g.n_blocks; j += MAX_BATCH) {
+    const int n = (int)std::min<long>(MAX_BATCH, g.n_blocks - j);
+    HIPC(gemm_store_batch<T>(emb, d, (const T*)b0.cak_w + j * wk, wk, n, (int)Lt, (int)d, (int)d,
+                             b0.cak_b + j * bk, bk, K + j * ks, d, ks, st));
+    HIPC(gemm_store_t_batch<T>(emb, d, (const T*)b0.cav_w + j * wv, wv, n, (int)Lt, (int)d, (int)d,
+                               b0.cav_b + j * bv, bv, VT + j * vs, m->Ltp, vs, st));
+    HIPC(rmsnorm_rope<T>(K + j * ks, Lt, d, (int)d, 1, b0.cak_gain + j * gk, nullptr, nullptr, 1, g.head_dim, st,
+                         {n, ks, gk}));
   }
   return CS_OK;
 }
