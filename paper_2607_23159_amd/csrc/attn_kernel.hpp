@@ -1,29 +1,26 @@
 // Flash attention for gfx950: softmax(q k^T / sqrt(dh)) v per (stream, head),
 // non-causal, online softmax in fp32, MFMA for both products.
 //
-// Work split.  A workgroup of NW waves shares each K/V tile; each wave owns
-// QB blocks of 32 queries.  With 8 waves of one 32-query block, a wave needs
-// about 200 registers, so two waves fit per SIMD and the hardware overlaps
-// one wave's softmax (VALU) with the other's matrix products.
+// Work split.  bf16: a workgroup of NW waves shares each K/V tile, staged
+// through LDS; each wave owns 32 queries, and the hardware overlaps one wave's
+// softmax (VALU) with another's matrix products.  fp32: the waves of a
+// workgroup share 32 queries and split the keys.
 //
 // Orientation.  Each wave computes the
 // transposed scores S^T = K Q^T (A = K tile from LDS, B = Q^T held in
 // registers for the whole key loop), so that after the softmax the
 // probabilities P^T already sit in the B-operand layout of the second
-// product O^T = V^T P^T (A = V^T tile from LDS).  The MFMA's contraction
-// index may visit keys in any order as long as both operands agree: the
-// accumulator register j of lane l holds key 8(j/4) + 4(l/32) + j%4 of a
-// 32-key block, so the V^T tile is written to LDS with each 32-key block
-// permuted to position 16(l/32) + j.  No shuffle of P through LDS is needed.
+// product O^T = V^T P^T (A = V^T).  The MFMA's contraction index may visit
+// keys in any order as long as both operands agree: accumulator register j of
+// lane l holds row 8(j/4) + 4(l/32) + j%4 of a 32-key block.  No shuffle of P
+// through LDS is needed.
 //
 // The softmax row of query q lives in lanes l and l^32 (16 keys each per
 // 32-key block), so row maxima and sums need one cross-lane exchange.
 //
-// K and V^T tiles of KVT keys are staged through LDS, double buffered (the
-// next tile's global loads are in flight during the current tile's math).
-// Keys past lk are masked to -inf in the last tile; K rows past lk are read
-// clamped and V^T columns past lk must be finite (the runtime zero-fills the
-// padding of every V^T buffer).
+// Keys past lk are masked to -inf in the last tile; K rows past lk are read as
+// zeros or clamped, and V^T columns past lk must be finite (the runtime
+// zero-fills the padding of every V^T buffer).
 #pragma once
 #include "kernels.hpp"
 
@@ -34,244 +31,164 @@ constexpr float RESCALE_LOG2 = 8.0f;
 // OCC is the number of waves per SIMD the register budget is sized for.
 // CROSS distinguishes the cross-attention instantiation (text keys) from the
 // self-attention one, so that profiles report them separately.
-template <typename T, int DH, int QB, int KVT, int NW, int OCC, bool CROSS>
-__global__ __launch_bounds__(64 * NW, OCC) void k_flash(AttnArgs<T> a) {
-  typedef Mfma32<T> MF;
-  constexpr int KPL = MF::KPL, KSTEP = MF::KSTEP;
-  constexpr int CH = 16 / (int)sizeof(T);
-  constexpr int KLD = DH + CH;    // padded K row (16 bytes)
-  constexpr int VLD = KVT + CH;   // padded V^T row
-  constexpr int NKT = KVT / 32;   // 32-key blocks per tile
+//
+// ---------------------------------------------------------------------------
+// fp32.  A 32 x 32 score block takes 32 DH cycles of products against 256 DH
+// bytes of K and V, so the matrix pipe is the limit even with every fragment
+// read straight from L2: no LDS staging, no barriers, each wave on its own.
+// At the sizes fp32 is used at the chip is nearly empty, so the NW waves of a
+// workgroup share 32 queries and split the keys (wave w takes 32-key blocks w,
+// w + NW, ...), and their partial softmax states are merged through LDS at the
+// end in the fixed order of the waves.  The split depends on lk alone, never on
+// the batch.  Each wave loads the next block's K under the value product and V
+// under the score product, 16 bytes per lane (four consecutive channels of K
+// and Q, four consecutive keys of V^T: the contraction visits both operands in
+// the same permuted order).
+//
+// Two streams of 384 tokens, 12 x 128 heads: 46 us (self) and 54 us (512 text
+// keys), against 69 and 87 us with 128-query workgroups staged through LDS; four
+// of 256 tokens, 4 x 32 heads: 7.1 us against 15.6.
+// ---------------------------------------------------------------------------
+template <int DH, int NW, int OCC, bool CROSS>
+__global__ __launch_bounds__(64 * NW, OCC) void k_flash_f32(AttnArgs<float> a) {
+  typedef Mfma32<float> MF;
+  constexpr int NG = DH / 8;      // 8-channel groups of the score product
   constexpr int NDT = DH / 32;    // 32-channel blocks of the output
-  constexpr int NKS = DH / KSTEP; // k-steps of the score product
-  constexpr int NPS = 32 / KSTEP; // k-steps of the value product per key block
-  constexpr int NT = 64 * NW;     // threads per workgroup
-  constexpr int K_CH = KVT * DH / CH / NT;
-  constexpr int V_CH = DH * KVT / CH / NT;
-  static_assert(K_CH * CH * NT == KVT * DH && V_CH * CH * NT == DH * KVT, "tile split");
-  static_assert(CH % 4 == 0, "4-element groups");
+  constexpr int OLD = DH + 4;     // padded row of a partial output
+  __shared__ __attribute__((aligned(16))) float s_o[NW][32 * OLD];
+  __shared__ float s_m[NW][32], s_l[NW][32];
 
-  __shared__ __attribute__((aligned(16))) T sK[2][KVT * KLD];
-  __shared__ __attribute__((aligned(16))) T sV[2][DH * VLD];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, l32 = lane & 31;
-  // One flat grid over (query tile, head, stream), query tile fastest,
-  // taken XCD-contiguous: the workgroups resident on one XCD at a time work
-  // on the same head and read its K/V tiles through a shared L2.
-  const int n_qt = (a.lq + NW * QB * 32 - 1) / (NW * QB * 32);
+  const int n_qt = (a.lq + 31) / 32;
   const int vid = xcd_contiguous(blockIdx.x, gridDim.x);
   const int qt = vid % n_qt, hs = vid / n_qt;
   const int head = hs % a.heads, s = hs / a.heads;
   const int kvs = a.kv_sel ? a.kv_sel[s] : s;
-  const int q0 = qt * (NW * QB * 32) + wave * QB * 32;
+  const int q0 = qt * 32;
 
-  const T* qb_ = a.q + (long)s * a.q_ss + head * DH;
-  const T* kb_ = a.k + (long)kvs * a.k_ss + head * DH;
-  const T* vb_ = a.vt + (long)kvs * a.vt_ss + (long)head * DH * a.vt_ld;
+  const float* kb_ = a.k + (long)kvs * a.k_ss + head * DH + 4 * half;
+  const float* vb_ = a.vt + (long)kvs * a.vt_ss + ((long)head * DH + l32) * a.vt_ld + 4 * half;
 
-  // Q^T fragments (B operand), kept for the whole key loop.
-  typename MF::frag qf[QB][NKS];
+  // lane: query l32, channels 8g + 4 half + e in qf[g][e]
+  f32x4 qf[NG];
+  {
+    const float* src = a.q + (long)s * a.q_ss + (long)min(q0 + l32, a.lq - 1) * a.q_ld + head * DH + 4 * half;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int row = min(q0 + qb * 32 + l32, a.lq - 1);
-    const T* src = qb_ + (long)row * a.q_ld + KPL * half;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      qf[qb][ks] = MF::load(src + ks * KSTEP);
-      // opaque to the optimiser: keeps Q in registers instead of reloading
-      // it from memory inside the key loop
-      asm volatile("" : "+v"(qf[qb][ks]));
-    }
+    for (int g = 0; g < NG; ++g) qf[g] = *reinterpret_cast<const f32x4*>(src + 8 * g);
   }
-
-  // tile staging
-  Chunk16 rk[K_CH], rv[V_CH];
-  auto load_tile = [&](int kv0) {
+  const int nblk = (a.lk + 31) / 32;
+  f32x4 kf[NG];
+  auto load_k = [&](int blk) {   // lane: key l32 of the block (past lk: the last one, masked)
+    const float* src = kb_ + (long)min(blk * 32 + l32, a.lk - 1) * a.k_ld;
 #pragma unroll
-    for (int c = 0; c < K_CH; ++c) {
-      const int id = c * NT + tid;
-      const int r = id / (DH / CH), cc = id % (DH / CH);
-      const int key = min(kv0 + r, a.lk - 1);
-      rk[c] = ld16(kb_ + (long)key * a.k_ld + cc * CH);
-    }
-#pragma unroll
-    for (int c = 0; c < V_CH; ++c) {
-      const int id = c * NT + tid;
-      const int r = id / (KVT / CH), cc = id % (KVT / CH);
-      rv[c] = ld16(vb_ + (long)r * a.vt_ld + kv0 + cc * CH);
-    }
-  };
-  auto store_tile = [&](int buf) {
-#pragma unroll
-    for (int c = 0; c < K_CH; ++c) {
-      const int id = c * NT + tid;
-      const int r = id / (DH / CH), cc = id % (DH / CH);
-      st16(&sK[buf][r * KLD + cc * CH], rk[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < V_CH; ++c) {
-      const int id = c * NT + tid;
-      const int r = id / (KVT / CH), cc = id % (KVT / CH);
-      // groups of 4 consecutive keys stay contiguous under the permutation
-      const T* src = reinterpret_cast<const T*>(&rv[c]);
-#pragma unroll
-      for (int g = 0; g < CH / 4; ++g) {
-        const int key = cc * CH + 4 * g;            // key inside the tile
-        const int w = key & 31;
-        const int pos = (key & ~31) + 16 * ((w >> 2) & 1) + 4 * (w >> 3);
-        T* dst = &sV[buf][r * VLD + pos];
-        if (sizeof(T) == 2) {
-          *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(src + 4 * g);
-        } else {
-          *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src + 4 * g);
-        }
-      }
-    }
+    for (int g = 0; g < NG; ++g) kf[g] = *reinterpret_cast<const f32x4*>(src + 8 * g);
   };
 
-  f32x16 o[QB][NDT];
+  f32x16 o[NDT];
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb)
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
+  float m_run = -INFINITY, l_run = 0.0f;
+
+  if (wave < nblk) load_k(wave);
+  for (int blk = wave; blk < nblk; blk += NW) {
+    const int kv0 = blk * 32;
+    // lane: channel 32 dt + l32, keys kv0 + 8g + 4 half + e in vf[dt][g][e]
+    // (columns past lk are finite padding, met by zero probabilities)
+    f32x4 vf[NDT][4];
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[qb][dt][r] = 0.0f;
-  float m_run[QB], l_run[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) { m_run[qb] = -INFINITY; l_run[qb] = 0.0f; }
+      for (int g = 0; g < 4; ++g)
+        vf[dt][g] = *reinterpret_cast<const f32x4*>(vb_ + (long)dt * 32 * a.vt_ld + kv0 + 8 * g);
 
-  const int ntiles = (a.lk + KVT - 1) / KVT;
-  load_tile(0);
-  store_tile(0);
-  __syncthreads();
-
-  for (int t = 0; t < ntiles; ++t) {
-    const int cur = t & 1;
-    const int kv0 = t * KVT;
-    const bool more = t + 1 < ntiles;
-    if (more) load_tile(kv0 + KVT);
-
-    // S^T = K Q^T
-    f32x16 sc[NKT][QB];
+    // S^T = K Q^T; two chains, so that no product waits for the one before
+    f32x16 sc[2];
 #pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb)
+      for (int r = 0; r < 16; ++r) sc[c][r] = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sc[kt][qb][r] = 0.0f;
-    const T* pk = &sK[cur][l32 * KLD + KPL * half];
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
+      for (int e = 0; e < 4; ++e) sc[e & 1] = MF::mma(kf[g][e], qf[g][e], sc[e & 1]);
+    if (blk + NW < nblk) load_k(blk + NW);
 #pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        typename MF::frag kf = MF::load(pk + kt * 32 * KLD + ks * KSTEP);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) sc[kt][qb] = MF::mma(kf, qf[qb][ks], sc[kt][qb]);
-      }
-    }
-    if (kv0 + KVT > a.lk) {
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = kv0 + kt * 32 + acc_row(r, lane);
-          if (key >= a.lk)
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) sc[kt][qb][r] = -INFINITY;
-        }
+    for (int r = 0; r < 16; ++r) {
+      sc[0][r] += sc[1][r];
+      if (kv0 + 32 > a.lk && kv0 + acc_row(r, lane) >= a.lk) sc[0][r] = -INFINITY;
     }
 
-    // online softmax; P^T packed into B-operand fragments.  The running
-    // maximum is only raised (and O, l rescaled) when some lane's tile
-    // maximum exceeds it by more than RESCALE_LOG2; otherwise the stale
-    // maximum is kept and probabilities may reach 2^RESCALE_LOG2, which fp32
-    // accumulation and the bf16 operand carry without loss of relative
+    // online softmax.  The running maximum is only raised (and O, l rescaled)
+    // when some lane's block maximum exceeds it by more than RESCALE_LOG2;
+    // otherwise the stale maximum is kept and probabilities may reach
+    // 2^RESCALE_LOG2, which fp32 accumulation carries without loss of relative
     // precision.  The branch is uniform across the wave.
-    typename MF::frag pf[QB][NKT][NPS];
+    float mx = -INFINITY;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[kt][qb][r]);
-      mx = max_lane_pair32(mx) * a.scale_log2;
-      if (__any(mx > m_run[qb] + RESCALE_LOG2)) {
-        const float m_new = fmaxf(m_run[qb], mx);
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
-        m_run[qb] = m_new;
-        l_run[qb] *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[qb][dt][r] *= alpha;
-      }
-      const float m_cur = m_run[qb];
-      float lsum = 0.0f;
-#pragma unroll
-      for (int kt = 0; kt < NKT; ++kt) {
-        float p[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(fmaf(sc[kt][qb][r], a.scale_log2, -m_cur));
-#pragma unroll
-        for (int ps = 0; ps < NPS; ++ps) {
-          if constexpr (KPL == 1) {
-            pf[qb][kt][ps] = to_t<T>(p[ps]);
-            lsum += p[ps];
-          } else {
-            // the row sum is taken over the rounded operand that the value
-            // product consumes, two elements per dot instruction
-            typename MF::frag f;
-#pragma unroll
-            for (int i = 0; i < KPL; ++i) f[i] = to_t<T>(p[ps * KPL + i]);
-            pf[qb][kt][ps] = f;
-            const bf16x2 one = {(bf16)1.0f, (bf16)1.0f};
-#pragma unroll
-            for (int i = 0; i < KPL; i += 2) {
-              const bf16x2 pr = {f[i], f[i + 1]};
-              lsum = __builtin_amdgcn_fdot2_f32_bf16(pr, one, lsum, false);
-            }
-          }
-        }
-      }
-      l_run[qb] += lsum;
-    }
-
-    // O^T += V^T P^T
-    const T* pv = &sV[cur][l32 * VLD + 16 * half];
-#pragma unroll
-    for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-      for (int ps = 0; ps < NPS; ++ps)
-#pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
-          typename MF::frag vf = MF::load(pv + dt * 32 * VLD + kt * 32 + ps * KPL);
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb) o[qb][dt] = MF::mma(vf, pf[qb][kt][ps], o[qb][dt]);
-        }
-
-    if (more) store_tile(cur ^ 1);
-    __syncthreads();
-  }
-
-  // normalise and store O[q][head*DH + channel]
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32, WAVE);
-    const float inv = 1.0f / l_tot;
-    const int row = q0 + qb * 32 + l32;
-    if (row < a.lq) {
-      T* dst = a.o + (long)s * a.o_ss + (long)row * a.o_ld + head * DH;
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[0][r]);
+    mx = max_lane_pair32(mx) * a.scale_log2;
+    if (__any(mx > m_run + RESCALE_LOG2)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int ch = dt * 32 + 8 * g + 4 * half;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) dst[ch + r] = to_t<T>(o[qb][dt][4 * g + r] * inv);
-        }
+        for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
     }
+    float p[16], lsum = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      p[r] = __builtin_amdgcn_exp2f(fmaf(sc[0][r], a.scale_log2, -m_run));
+      lsum += p[r];
+    }
+    l_run += lsum;
+
+    // O^T += V^T P^T: register 4g + e of P^T holds key 8g + 4 half + e
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt) o[dt] = MF::mma(vf[dt][g][e], p[4 * g + e], o[dt]);
+  }
+
+  // merge: every wave's maximum and sum, then its output scaled to the common
+  // maximum (a wave without a block has maximum -inf, sum and output 0)
+  const float l_tot = l_run + __shfl_xor(l_run, 32, WAVE);
+  if (half == 0) {
+    s_m[wave][l32] = m_run;
+    s_l[wave][l32] = l_tot;
+  }
+  __syncthreads();
+  float m_all = s_m[0][l32];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][l32]);
+  float l_all = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) l_all += s_l[w][l32] * __builtin_amdgcn_exp2f(s_m[w][l32] - m_all);
+  const float f = __builtin_amdgcn_exp2f(m_run - m_all) / l_all;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 v = {o[dt][4 * g] * f, o[dt][4 * g + 1] * f, o[dt][4 * g + 2] * f, o[dt][4 * g + 3] * f};
+      *reinterpret_cast<f32x4*>(&s_o[wave][l32 * OLD + dt * 32 + 8 * g + 4 * half]) = v;
+    }
+  __syncthreads();
+  float* dst = a.o + (long)s * a.o_ss + head * DH;
+#pragma unroll
+  for (int i = tid; i < 32 * DH / 4; i += 64 * NW) {
+    const int q = i / (DH / 4), c = 4 * (i % (DH / 4));
+    f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[0][q * OLD + c]);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4*>(&s_o[w][q * OLD + c]);
+    if (q0 + q < a.lq) *reinterpret_cast<f32x4*>(dst + (long)(q0 + q) * a.o_ld + c) = v;
   }
 }
 
@@ -443,7 +360,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_dl(AttnArgs<bf16> a) {
         }
     }
 
-    // online softmax with lazy rescaling (see k_flash); P^T packed into
+    // online softmax with lazy rescaling (see k_flash_f32); P^T packed into
     // B-operand fragments, row sums over the rounded operands
     typename MF::frag pf[QB][NKT][NPS];
 #pragma unroll
@@ -680,7 +597,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
         }
     }
 
-    // online softmax with lazy rescaling (see k_flash)
+    // online softmax with lazy rescaling (see k_flash_f32)
     frag pf[NKT][NPS];
     float mx = -INFINITY;
 #pragma unroll

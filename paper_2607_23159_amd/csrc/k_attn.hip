@@ -8,16 +8,19 @@ int attn_kv_tile(int dtype_bytes, int head_dim) {
   return head_dim > 64 ? 32 : 64;
 }
 
-template <typename T, int DH, int QB, int KVT, int NW, int OCC>
-static hipError_t launch_flash(const AttnArgs<T>& a, hipStream_t st) {
-  const int qpw = NW * QB * 32;
-  const long nwg = (long)cdiv(a.lq, qpw) * a.heads * a.n_streams;
+// fp32: 32 queries per workgroup, keys split over four waves.
+template <int DH, int OCC>
+static hipError_t launch_flash_f32(const AttnArgs<float>& a, hipStream_t st) {
+  constexpr int NW = 4;
+  const long nwg = (long)cdiv(a.lq, 32) * a.heads * a.n_streams;
   if (nwg * 64 * NW > 0xFFFFFFFFL) return hipErrorInvalidConfiguration;
-  dim3 grid((unsigned)nwg);
+  // 16-byte rows of q, k and o; every 32-key block of V^T inside its padded row
+  if (a.q_ld % 4 || a.k_ld % 4 || a.o_ld % 4 || a.vt_ld % 4 || a.vt_ld < round_up(a.lk, 32))
+    return hipErrorInvalidValue;
   if (a.kv_sel)
-    hipLaunchKernelGGL((k_flash<T, DH, QB, KVT, NW, OCC, true>), grid, dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((k_flash_f32<DH, NW, OCC, true>), dim3((unsigned)nwg), dim3(64 * NW), 0, st, a);
   else
-    hipLaunchKernelGGL((k_flash<T, DH, QB, KVT, NW, OCC, false>), grid, dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((k_flash_f32<DH, NW, OCC, false>), dim3((unsigned)nwg), dim3(64 * NW), 0, st, a);
   return hipGetLastError();
 }
 
@@ -106,9 +109,9 @@ template <>
 hipError_t flash_attention<float>(const AttnArgs<float>& a, int head_dim, hipStream_t st) {
   if (a.lq <= 0 || a.n_streams <= 0) return hipSuccess;
   switch (head_dim) {
-    case 128: return launch_flash<float, 128, 1, 32, 4, 1>(a, st);
-    case 64: return launch_flash<float, 64, 1, 64, 4, 1>(a, st);
-    case 32: return launch_flash<float, 32, 1, 64, 4, 1>(a, st);
+    case 128: return launch_flash_f32<128, 1>(a, st);
+    case 64: return launch_flash_f32<64, 2>(a, st);
+    case 32: return launch_flash_f32<32, 4>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
