@@ -134,8 +134,8 @@ CS_DEV void gemm_tile_of(int tiles_m, int tiles_n, int& tm_i, int& tn_i) {
 
 // ---------------------------------------------------------------------------
 // bf16 GEMM, 4 waves of (BM/2) x (BN/2): one wave per SIMD at BM x BN = 256 x
-// 256, 192 x 256 and 128 x 256, two workgroups per CU (OCC = 2) at 128 x 128
-// and three at 64 x 64; the accumulators are held in AGPRs.
+// 256 and 192 x 256, two workgroups per CU (OCC = 2) at 128 x 128 and three at
+// 64 x 64; the accumulators are held in AGPRs.
 //
 // Fragment reads from LDS per product: (BM/32 + 8) reads per BM/4 products,
 // against 12 per 32 with 8 waves of 128x64, so the LDS, which also absorbs
@@ -351,19 +351,23 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_w4(const bf16* __restrict__ A
 
 // ---------------------------------------------------------------------------
 // GEMM on a ring of LDS stages.  In bf16 for small grids (few rows, narrow
-// outputs): BM x BN tiles of 64 x 64 (8 waves of 32 x 16), 32 x 64 and 32 x 32
-// (4 waves).  In fp32 for all of them.
+// outputs): BM x BN tiles of 128 x 128, 64 x 128 and 64 x 64 (8 waves), 32 x 64
+// and 32 x 32 (4 waves).  In fp32 for all of them.
 //
 // With a tile or less per CU nothing runs beside it, so a slice costs its
 // latency chain: barrier, fragment reads, products.  The chain is shortened in
-// three ways: one step covers two K slices (SL), so the barrier and the read
-// latency are paid half as often; the reads of step k+1 are issued before the
+// three ways: one step covers two K slices (SL; one at 128 x 128, whose
+// products cover the latency), so the barrier and the read latency are paid
+// half as often; the reads of step k+1 are issued before the
 // products of step k, into a second register set; and STAGES steps of loads
 // are in flight (the buffer of step k is free as soon as its reads are done,
 // before its products).  Measured at 384 x 1536 x 8960, one stream of 384
 // tokens on the 1.3B FFN-down projection, 144 tiles of 64 x 64: 30 us, against
 // 156 us with 256 x 256 tiles (12 of them) and 41 us with one slice per
-// barrier; 891 x 256 x 512 with 32 x 32 tiles: 3.4 us against 24.8 us.
+// barrier; 891 x 256 x 512 with 32 x 32 tiles: 3.4 us against 24.8 us.  With
+// weights from HBM the loads in flight count too: 1536 x 1536 x 8960 takes 70 us
+// with 128 x 128 ring tiles (three slices ahead) against 94 us with k_gemm_w4's
+// (one and a half), 384 x 4608 x 1536 13.7 us with 64 x 128 against 17.9 us.
 //
 // In fp32 a 32 x 32 x 32 slice of products takes 256 cycles per CU, ten times
 // the fragment reads, and the matrix pipe is the limit whatever the tile: the
@@ -653,7 +657,6 @@ template <typename T> struct EpiQKV {
   CS_DEV void store_v_transposed(const f32x4 (&acc)[TM][TN], bf16* stage, int row_base,
                                  int col_base, int lane, int M, int N) const {
     constexpr int R = TM * 16, C = TN * 16, SP = R + 8, CHUNKS = R / 8;
-    static_assert(64 % CHUNKS == 0 && C % (64 / CHUNKS) == 0, "readback split");
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -662,18 +665,20 @@ template <typename T> struct EpiQKV {
         for (int r = 0; r < 4; ++r)
           stage[(16 * j + 4 * (lane >> 4) + r) * SP + 16 * i + (lane & 15)] = to_t<T>(acc[i][j][r]);
     __syncthreads();
-    // lane: tokens row0..row0+7 of channels c = CPI*q + lane / CHUNKS
+    // lane: tokens row0..row0+7 of channels c = CPI*q + lane / CHUNKS (with 96
+    // rows, 12 chunks, the last 4 lanes have none)
     constexpr int CPI = 64 / CHUNKS;
+    if (lane >= CPI * CHUNKS) return;
     const int k = lane % CHUNKS;
     const int row0 = row_base + 8 * k;
     const int s = row0 / L, tok = row0 - s * L;
     const bool whole = row0 + 8 <= M && tok + 8 <= L;   // one stream, all rows valid
     T* const base = vt + (long)s * vt_ss + tok;
 #pragma unroll 4
-    for (int q = 0; q < C / CPI; ++q) {
+    for (int q = 0; q < (C + CPI - 1) / CPI; ++q) {
       const int c = CPI * q + lane / CHUNKS;
       const int col = col_base + c;
-      if (col >= N) continue;
+      if (c >= C || col >= N) continue;
       const bf16x8 v = *reinterpret_cast<const bf16x8*>(stage + c * SP + 8 * k);
       T* dst = base + (long)(col - 2 * d) * vt_ld;
       if (whole && ((uintptr_t)dst & 15) == 0) {

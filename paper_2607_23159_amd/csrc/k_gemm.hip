@@ -53,34 +53,36 @@ hipError_t gemm_tile_weight(const float* src, int N, int K, T* dst, hipStream_t 
 template <class Epi> struct EpiIsResidual : std::false_type {};
 template <int G> struct EpiIsResidual<EpiResidual<G>> : std::true_type {};
 template <int G, typename T> struct EpiIsResidual<EpiResidualStore<G, T>> : std::true_type {};
-// The transposed part of the QKV epilogue needs power-of-two wave tiles.
-template <class Epi> struct EpiAllows192 : std::true_type {};
-template <typename T> struct EpiAllows192<EpiQKV<T>> : std::false_type {};
-
-enum Bf16Tile { W4_256x256, W4_192x256, W4_128x256, W4_128x128, W4_64x64, RING_64x64, RING_32x64, RING_32x32, N_TILES };
+enum Bf16Tile {
+  W4_256x256, W4_192x256, W4_128x128, W4_64x64,
+  RING_128x128, RING_64x128, RING_64x64, RING_32x64, RING_32x32, N_TILES
+};
 
 // Time of a launch per tile shape, in us:
 //   fixed + rounds * (K/64 * full + epi) + K/64 * (lone + (full - lone) * r) + epi * (1 + r) / 2
 // where a round fills `slots` workgroups on each of the 256 CUs, r is the
 // filled part of the last round (left out when 0), `lone` and `full` are the
 // time per K slice of 64 of a tile alone on its CU and of a full chip, and epi
-// grows by epi_res for residual updates.  The constants are a least-squares
-// fit to 428 measured shapes (64 to 65,520 rows; N and K of the tiny, ragged,
-// 1.3B, 5B and 14B projections; bf16 stores and residual updates) that
-// reproduces each shape's times within 4 to 11%.  The choice it makes costs
-// 1.5% on average over those 428 (at most 24%, at launches under 20 us)
-// against the best tile of each, where 256 x 256 tiles for everything took 2.3
+// grows by epi_res for residual updates.  The constants are a least-squares fit
+// to 697 measured shapes (32 to 12,480 rows; N and K of projections at widths
+// 128 to 5120 and of the heads; bf16 stores and residual updates), each launch
+// on another copy of the weights out of 900 MB: in a model a layer's weights
+// come from HBM, which shifts the choice towards shapes with more loads in
+// flight.  They were then adjusted for the choice rather than for the times:
+// it costs 1.0% on average over the 697 (at most 20%, at launches of 20 us)
+// against the best tile of each, where 256 x 256 tiles for everything took 3.2
 // times as long on average.
 struct TileCost { int bm, bn, slots; double lone, full, fixed, epi, epi_res; };
 static const TileCost TILE_COST[N_TILES] = {
-    {256, 256, 1, 0.907, 1.336, 3.32, 7.90, 16.5},
-    {192, 256, 1, 0.720, 1.038, 2.87, 6.32, 11.0},
-    {128, 256, 1, 0.544, 0.761, 2.57, 4.42, 7.19},
-    {128, 128, 2, 0.326, 0.838, 1.83, 3.39, 4.53},
-    {64, 64, 3, 0.183, 0.531, 1.96, 1.20, 1.30},
-    {64, 64, 1, 0.187, 0.204, 1.91, 1.53, 0.61},
-    {32, 64, 2, 0.137, 0.248, 2.09, 1.06, 0.50},
-    {32, 32, 2, 0.113, 0.203, 2.02, 0.79, 0.16},
+    {256, 256, 1, 0.879, 1.136, 3.65, 7.42, 18.9},
+    {192, 256, 1, 0.947, 1.053, 3.05, 5.59, 10.2},
+    {128, 128, 2, 0.523, 0.864, 1.51, 3.36, 4.13},
+    {64, 64, 3, 0.355, 0.561, 1.53, 1.15, 1.00},
+    {128, 128, 1, 0.343, 0.464, 1.73, 3.59, 2.69},
+    {64, 128, 1, 0.331, 0.349, 1.78, 2.24, 1.11},
+    {64, 64, 1, 0.200, 0.222, 1.80, 1.54, 0.38},
+    {32, 64, 2, 0.166, 0.285, 1.77, 1.07, 0.25},
+    {32, 32, 2, 0.167, 0.238, 1.72, 0.77, 0.00},
 };
 // From two rounds of 256 x 256 tiles on, the chip's power limit evens out a
 // partly filled last round (idle CUs let the others clock higher), so only 192
@@ -90,7 +92,7 @@ static const TileCost TILE_COST[N_TILES] = {
 constexpr long LARGE_TILES = 512, LARGE_MIN_N = 1024;
 constexpr double LARGE_MARGIN = 0.97;
 
-static Bf16Tile choose_tile(long M, long N, long K, long batch, bool residual, bool allow_192) {
+static Bf16Tile choose_tile(long M, long N, long K, long batch, bool residual) {
   const double nk = (double)(K / SLICE_K<bf16>);
   auto cost = [&](int i) {
     const TileCost& c = TILE_COST[i];
@@ -102,11 +104,10 @@ static Bf16Tile choose_tile(long M, long N, long K, long batch, bool residual, b
   };
   const long tiles256 = (long)cdiv(M, 256) * cdiv(N, 256) * batch;
   if (tiles256 >= LARGE_TILES && N >= LARGE_MIN_N)
-    return allow_192 && cost(W4_192x256) < LARGE_MARGIN * cost(W4_256x256) ? W4_192x256 : W4_256x256;
+    return cost(W4_192x256) < LARGE_MARGIN * cost(W4_256x256) ? W4_192x256 : W4_256x256;
   int best = W4_256x256;
   double best_t = cost(best);
   for (int i = 0; i < N_TILES; ++i) {
-    if (i == W4_192x256 && !allow_192) continue;
     const double t = cost(i);
     if (t < best_t) { best = i; best_t = t; }
   }
@@ -123,11 +124,11 @@ static void launch_w4(const bf16* A, long lda, const bf16* W, int M, int N, int 
                      W, M, N, K, b.w_stride, epi);
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int STAGES, int OCC, class Epi>
+template <typename T, int BM, int BN, int WGM, int WGN, int SL, int STAGES, int OCC, class Epi>
 static void launch_ring(const T* A, long lda, const T* W, int M, int N, int K, GemmBatch b, const Epi& epi,
                         hipStream_t st) {
   const unsigned tiles = (unsigned)((long)cdiv(M, BM) * cdiv(N, BN));
-  hipLaunchKernelGGL((k_gemm_ring<T, BM, BN, WGM, WGN, 2, STAGES, OCC, GROUP_M, Epi>), dim3(tiles, (unsigned)b.n),
+  hipLaunchKernelGGL((k_gemm_ring<T, BM, BN, WGM, WGN, SL, STAGES, OCC, GROUP_M, Epi>), dim3(tiles, (unsigned)b.n),
                      dim3(64 * WGM * WGN), 0, st, A, lda, W, M, N, K, b.w_stride, epi);
 }
 
@@ -146,27 +147,26 @@ static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, 
   // per-tile buffer ranges are 32-bit byte counts
   if ((long)W_BLOCK_ROWS * std::max(lda, (long)K) * (long)sizeof(T) > 0x7FFFFFFFL) return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 2) {
-    constexpr bool RES = EpiIsResidual<Epi>::value, A192 = EpiAllows192<Epi>::value;
+    constexpr bool RES = EpiIsResidual<Epi>::value;
     // residual operands in flight per wave: with one wave per SIMD nothing
     // else hides their latency, with two workgroups per CU half as many do
     constexpr int PD = RES ? 8 : 2, PD2 = RES ? 4 : 2;
-    switch (choose_tile(M, N, K, b.n, RES, A192)) {
+    switch (choose_tile(M, N, K, b.n, RES)) {
       case W4_256x256: launch_w4<256, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
-      case W4_192x256:
-        if constexpr (A192) launch_w4<192, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st);
-        break;
-      case W4_128x256: launch_w4<128, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
+      case W4_192x256: launch_w4<192, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
       case W4_128x128: launch_w4<128, 128, 2, PD2>(A, lda, W, M, N, K, b, epi, st); break;
       case W4_64x64: launch_w4<64, 64, 3, 2>(A, lda, W, M, N, K, b, epi, st); break;
-      case RING_64x64: launch_ring<T, 64, 64, 2, 4, 4, 2>(A, lda, W, M, N, K, b, epi, st); break;
-      case RING_32x64: launch_ring<T, 32, 64, 1, 4, 3, 2>(A, lda, W, M, N, K, b, epi, st); break;
-      default: launch_ring<T, 32, 32, 2, 2, 4, 2>(A, lda, W, M, N, K, b, epi, st);
+      case RING_128x128: launch_ring<T, 128, 128, 2, 4, 1, 4, 2>(A, lda, W, M, N, K, b, epi, st); break;
+      case RING_64x128: launch_ring<T, 64, 128, 2, 4, 2, 3, 2>(A, lda, W, M, N, K, b, epi, st); break;
+      case RING_64x64: launch_ring<T, 64, 64, 2, 4, 2, 4, 2>(A, lda, W, M, N, K, b, epi, st); break;
+      case RING_32x64: launch_ring<T, 32, 64, 1, 4, 2, 3, 2>(A, lda, W, M, N, K, b, epi, st); break;
+      default: launch_ring<T, 32, 32, 2, 2, 2, 4, 2>(A, lda, W, M, N, K, b, epi, st);
     }
   } else {
     if ((long)cdiv(M, 64) * cdiv(N, 64) * b.n >= F32_64_TILES)
-      launch_ring<T, 64, 64, 2, 4, 2, 4>(A, lda, W, M, N, K, b, epi, st);
+      launch_ring<T, 64, 64, 2, 4, 2, 2, 4>(A, lda, W, M, N, K, b, epi, st);
     else
-      launch_ring<T, 32, 32, 2, 2, 2, 4>(A, lda, W, M, N, K, b, epi, st);
+      launch_ring<T, 32, 32, 2, 2, 2, 2, 4>(A, lda, W, M, N, K, b, epi, st);
   }
   return hipGetLastError();
 }
