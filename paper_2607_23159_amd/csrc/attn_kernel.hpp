@@ -439,6 +439,32 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_dl(AttnArgs<bf16> a) {
 }
 
 
+// O^T accumulators of a wave's 32 queries, normalised and stored as row
+// query l32 of dst (row stride o_ld).  A lane holds 4 consecutive channels per
+// group of 8 and the lane 32 away the other 4: exchanging them between two
+// groups (v_permlane32_swap) gives each lane 8 consecutive channels of one
+// group, one 16-byte store instead of two of 8 bytes.  Measured with the Q
+// loads behind the first tile's: 32,760 queries x 512 keys x 12 heads, 8
+// streams 1045 -> 988 us, one stream 159 -> 144 us; 384 x 512, one stream 19.9
+// -> 17.6 us; neutral over 32,760 keys (bitwise equal).
+template <int NDT>
+CS_DEV void store_o_rows(const f32x16 (&o)[NDT], float inv, bf16* dst, int half, bool valid) {
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; g += 2) {
+      union { bf16x4 v; uint32_t u[2]; } x, y;   // groups g and g + 1
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        x.v[r] = (bf16)(o[dt][4 * g + r] * inv);
+        y.v[r] = (bf16)(o[dt][4 * g + 4 + r] * inv);
+      }
+      const auto w0 = __builtin_amdgcn_permlane32_swap(x.u[0], y.u[0], false, false);
+      const auto w1 = __builtin_amdgcn_permlane32_swap(x.u[1], y.u[1], false, false);
+      if (valid) *reinterpret_cast<uint4*>(dst + dt * 32 + 8 * (g + half)) = make_uint4(w0[0], w1[0], w0[1], w1[1]);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // bf16 variant with padded LDS rows (head dims 64 and 128).
 //
@@ -455,13 +481,19 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_dl(AttnArgs<bf16> a) {
 // whole 1 KB load instructions, spread over the waves (the first few waves
 // issue one more than the others).  Results are bitwise those of k_flash_dl.
 //
-// Occupancy.  The V^T fragments are read inside the value product, each just
-// before its two MFMAs, instead of all ahead of the softmax: that saves 64
-// registers and brings a wave to 160, so three waves fit per SIMD (12 waves
-// of 32 queries per workgroup).  The third wave hides LDS latency better than
-// the early reads did (measured 4% faster at 32,760 tokens).
+// Occupancy.  With 12 waves of 32 queries the V^T fragments are read inside
+// the value product, each just before its MFMA, instead of all ahead of the
+// softmax: that saves 64 registers and brings a wave to 160, so three waves
+// fit per SIMD, and the third wave hides LDS latency better than early reads
+// (measured 4% faster at 32,760 tokens).  With 8 waves (two per SIMD, 256
+// registers) a tile's K fragments are requested together and its V^T fragments
+// ahead of the softmax (EARLY: 5711 -> 5583 us, one 32,760-token stream).  4
+// waves, one per SIMD, are for grids that leave CUs idle otherwise: 384 tokens
+// x 12 heads 12.4 us against 14.8 with 8 waves and 19.0 with 12.
+//
+// The first tile is requested before Q, so that their latencies overlap.
 // ---------------------------------------------------------------------------
-template <int DH, int NW, int OCC, int STAGES, bool CROSS>
+template <int DH, int NW, int OCC, int STAGES, bool EARLY, bool CROSS>
 __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
   typedef Mfma32<bf16> MF;
   typedef typename MF::frag frag;
@@ -491,18 +523,6 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
   const bf16* qb_ = a.q + (long)s * a.q_ss + head * DH;
   const bf16* kb_ = a.k + (long)kvs * a.k_ss + head * DH;
   const bf16* vb_ = a.vt + (long)kvs * a.vt_ss + (long)head * DH * a.vt_ld;
-
-  // Q^T fragments (B operand), kept for the whole key loop
-  frag qf[NKS];
-  {
-    const int row = min(q0 + l32, a.lq - 1);
-    const bf16* src = qb_ + (long)row * a.q_ld + MF::KPL * half;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      qf[ks] = MF::load(src + ks * KSTEP);
-      asm volatile("" : "+v"(qf[ks]));
-    }
-  }
 
   // load instruction i of this wave fills slots [64g, 64g + 64) of the stage,
   // g = wave + NW*i; slot p of the K part is row p / CK, chunk p % CK (the
@@ -546,8 +566,20 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
   float m_run = -INFINITY, l_run = 0.0f;
 
   const int ntiles = (a.lk + KVT - 1) / KVT;
+  issue(0, 0);
+  // Q^T fragments (B operand), kept for the whole key loop
+  frag qf[NKS];
+  {
+    const int row = min(q0 + l32, a.lq - 1);
+    const bf16* src = qb_ + (long)row * a.q_ld + MF::KPL * half;
 #pragma unroll
-  for (int t = 0; t < STAGES - 1; ++t)
+    for (int ks = 0; ks < NKS; ++ks) {
+      qf[ks] = MF::load(src + ks * KSTEP);
+      asm volatile("" : "+v"(qf[ks]));
+    }
+  }
+#pragma unroll
+  for (int t = 1; t < STAGES - 1; ++t)
     if (t < ntiles) issue(t, t);
 
   // fragment bases: the score product reads K row pi(l32) of each 32-key
@@ -575,6 +607,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
     const int kv0 = t * KVT;
 
     // S^T = K Q^T (rows in pi order)
+    frag kf[EARLY ? NKS : 1][NKT];
+    if constexpr (EARLY) {
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt)
+          kf[ks][kt] = MF::load(reinterpret_cast<const bf16*>(pk + kt * 32 * KRS + ks * 32));
+    }
     f32x16 sc[NKT];
 #pragma unroll
     for (int kt = 0; kt < NKT; ++kt)
@@ -584,9 +624,23 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
     for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt) {
-        frag kf = MF::load(reinterpret_cast<const bf16*>(pk + kt * 32 * KRS + ks * 32));
-        sc[kt] = MF::mma(kf, qf[ks], sc[kt]);
+        if constexpr (EARLY)
+          sc[kt] = MF::mma(kf[ks][kt], qf[ks], sc[kt]);
+        else
+          sc[kt] = MF::mma(MF::load(reinterpret_cast<const bf16*>(pk + kt * 32 * KRS + ks * 32)), qf[ks], sc[kt]);
       }
+    auto load_v = [&](int kt, int ps, int dt) {
+      return MF::load(reinterpret_cast<const bf16*>(pv + dt * 32 * VRS + kt * 64 + ps * 32));
+    };
+    frag vf[EARLY ? NKT : 1][NPS][NDT];
+    if constexpr (EARLY) {
+#pragma unroll
+      for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+        for (int ps = 0; ps < NPS; ++ps)
+#pragma unroll
+          for (int dt = 0; dt < NDT; ++dt) vf[kt][ps][dt] = load_v(kt, ps, dt);
+    }
     if (kv0 + KVT > a.lk) {
 #pragma unroll
       for (int kt = 0; kt < NKT; ++kt)
@@ -636,35 +690,23 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
     }
     l_run += lsum;
 
-    // O^T += V^T P^T, each V^T fragment read just before its product
+    // O^T += V^T P^T
 #pragma unroll
     for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
       for (int ps = 0; ps < NPS; ++ps)
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
-          const frag vf = MF::load(reinterpret_cast<const bf16*>(pv + dt * 32 * VRS + kt * 64 + ps * 32));
-          o[dt] = MF::mma(vf, pf[kt][ps], o[dt]);
+          if constexpr (EARLY)
+            o[dt] = MF::mma(vf[kt][ps][dt], pf[kt][ps], o[dt]);
+          else
+            o[dt] = MF::mma(load_v(kt, ps, dt), pf[kt][ps], o[dt]);
         }
   }
 
-  // normalise and store O[q][head*DH + channel]
   const float l_tot = l_run + __shfl_xor(l_run, 32, WAVE);
-  const float inv = 1.0f / l_tot;
   const int row = q0 + l32;
-  if (row < a.lq) {
-    bf16* dst = a.o + (long)s * a.o_ss + (long)row * a.o_ld + head * DH;
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int ch = dt * 32 + 8 * g + 4 * half;
-        bf16x4 q;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) q[r] = (bf16)(o[dt][4 * g + r] * inv);
-        *reinterpret_cast<bf16x4*>(dst + ch) = q;
-      }
-  }
+  store_o_rows(o, 1.0f / l_tot, a.o + (long)s * a.o_ss + (long)row * a.o_ld + head * DH, half, row < a.lq);
 }
 
 }  // namespace cs

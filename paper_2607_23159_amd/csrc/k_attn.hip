@@ -44,15 +44,16 @@ static hipError_t launch_flash_dl(const AttnArgs<bf16>& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// bf16, head dims 64 and 128: padded-row tiles of 64 keys in a 3-deep ring
-// (105 KB of LDS at 128: one workgroup per CU), 32 queries per wave.  Twelve
-// waves (three per SIMD) are the faster shape per query; eight waves (two per
-// SIMD) take 256 instead of 384 queries per workgroup, which matters when the
-// grid is a few rounds of the CUs long: at one 32,760-token stream of 12 heads,
-// 1032 twelve-wave workgroups fill 256 CUs 4.03 times (five rounds) while 1536
-// eight-wave ones fill them exactly six times.  Each wave's arithmetic is the
-// same in both shapes (same key order, same per-wave rescale decisions), so
-// the outputs are bitwise equal and the choice never changes a result.
+// bf16, head dims 64 and 128: padded-row tiles of 64 keys in a 3-deep ring (4
+// waves: 4-deep), 105 to 140 KB of LDS at 128: one workgroup per CU.  12 waves
+// of 32 queries (three per SIMD) are the fastest shape per query; 8 (two per
+// SIMD) and 4 (one) take 256 and 128 instead of 384 queries per workgroup,
+// which matters when the grid is a few rounds of the CUs long or shorter than
+// one: at one 32,760-token stream of 12 heads, 1032 twelve-wave workgroups fill
+// 256 CUs 4.03 times while 1536 eight-wave ones fill them exactly six times.
+// Each wave's arithmetic is the same in all shapes (same key order, same
+// per-wave rescale decisions), so the outputs are bitwise equal and the choice
+// never changes a result.
 static int cu_count() {
   static int cus[64] = {0};
   int dev = 0;
@@ -65,17 +66,15 @@ static int cu_count() {
   return cus[dev];
 }
 
-template <int DH, int NW, int OCC>
+template <int DH, int NW, int OCC, int STAGES, bool EARLY>
 static hipError_t launch_flash_pad_nw(const AttnArgs<bf16>& a, hipStream_t st) {
-  constexpr int STAGES = 3;
   const long nwg = (long)cdiv(a.lq, NW * 32) * a.heads * a.n_streams;
   if (nwg * 64 * NW > 0xFFFFFFFFL) return hipErrorInvalidConfiguration;
   if (a.kv_sel)
-    hipLaunchKernelGGL((k_flash_pad<DH, NW, OCC, STAGES, true>), dim3((unsigned)nwg), dim3(64 * NW), 0,
-                       st, a);
+    hipLaunchKernelGGL((k_flash_pad<DH, NW, OCC, STAGES, EARLY, true>), dim3((unsigned)nwg), dim3(64 * NW), 0, st, a);
   else
-    hipLaunchKernelGGL((k_flash_pad<DH, NW, OCC, STAGES, false>), dim3((unsigned)nwg), dim3(64 * NW), 0,
-                       st, a);
+    hipLaunchKernelGGL((k_flash_pad<DH, NW, OCC, STAGES, EARLY, false>), dim3((unsigned)nwg), dim3(64 * NW), 0, st,
+                       a);
   return hipGetLastError();
 }
 
@@ -83,15 +82,23 @@ template <int DH>
 static hipError_t launch_flash_pad(const AttnArgs<bf16>& a, hipStream_t st) {
   if ((long)a.lk * a.k_ld * 2 > 0x7FFFFFFFL || (long)DH * a.vt_ld * 2 > 0x7FFFFFFFL)
     return hipErrorInvalidValue;
-  // every 64-key tile of V^T must lie inside its padded row
-  if (a.vt_ld < round_up(a.lk, 64)) return hipErrorInvalidValue;
-  // estimated time in rounds of the CUs x queries per workgroup; eight waves
-  // run about 3.5% slower per query than twelve
+  // every 64-key tile of V^T must lie inside its padded row; outputs are
+  // stored 16 bytes at a time
+  if (a.vt_ld < round_up(a.lk, 64) || a.o_ld % 8 || a.o_ss % 8) return hipErrorInvalidValue;
+  // Estimated time: rounds of the CUs x queries per workgroup x time per query
+  // against 12 waves (8 waves 6%, 4 waves 55% more: 5.33, 5.58 and 7.74 ms for
+  // one stream in whole rounds).  A partly filled last round costs at least 0.7
+  // of a full one (12 waves, 4.03 rounds: 6.29 ms).
   const long cus = cu_count(), sh = (long)a.heads * a.n_streams;
-  const double t12 = (double)cdiv(cdiv(a.lq, 384) * sh, cus) * 384.0;
-  const double t8 = (double)cdiv(cdiv(a.lq, 256) * sh, cus) * 256.0 * 1.035;
-  if (t8 < t12) return launch_flash_pad_nw<DH, 8, 2>(a, st);
-  return launch_flash_pad_nw<DH, 12, 3>(a, st);
+  auto cost = [&](int queries, double per_query) {
+    const long nwg = (long)cdiv(a.lq, queries) * sh;
+    const double r = (double)(nwg % cus) / (double)cus;
+    return ((double)(nwg / cus) + (r > 0 ? 0.7 + 0.3 * r : 0.0)) * queries * per_query;
+  };
+  const double t12 = cost(384, 1.0), t8 = cost(256, 1.06), t4 = cost(128, 1.55);
+  if (t4 < t8 && t4 < t12) return launch_flash_pad_nw<DH, 4, 1, 4, false>(a, st);
+  if (t8 < t12) return launch_flash_pad_nw<DH, 8, 2, 3, true>(a, st);
+  return launch_flash_pad_nw<DH, 12, 3, 3, false>(a, st);
 }
 
 template <>
