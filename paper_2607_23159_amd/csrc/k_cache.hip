@@ -91,16 +91,19 @@ CS_DEV void wave_stream_sums(const double* __restrict__ ps, int nchunk, double& 
 
 constexpr int FIN_WAVES = 16;
 
+// What the host needs of the decision (mask, indicators, count) is written to
+// pinned host memory by the kernel itself: the copy that followed it cost a
+// launch and its latency in the one place of a step that the host waits for.
+
 __global__ __launch_bounds__(64 * FIN_WAVES) void k_decide_finalize(DecideParams p,
                                                          const double* __restrict__ partials,
                                                          const uint8_t* __restrict__ ovr,
                                                          double* __restrict__ a,
                                                          uint8_t* __restrict__ has_ref,
                                                          uint8_t* __restrict__ mask,
-                                                         double* __restrict__ a_seen,
                                                          int32_t* __restrict__ slots,
                                                          int32_t* __restrict__ branch,
-                                                         DecideOut* __restrict__ out) {
+                                                         DecideHost host) {
   __shared__ double sums[2 * MAX_DECIDE_STREAMS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (p.use_partials) {
@@ -142,7 +145,10 @@ __global__ __launch_bounds__(64 * FIN_WAVES) void k_decide_finalize(DecideParams
         has_ref[s] = 1;
       }
       mask[s] = compute ? 1 : 0;
-      a_seen[s] = seen;
+      if (host.n_compute) {
+        host.mask[s] = compute ? 1 : 0;
+        host.a_seen[s] = seen;
+      }
     }
     const unsigned long long bal = __ballot(valid && compute);
     const unsigned long long below = lane == 0 ? 0ull : (bal & ((1ull << lane) - 1ull));
@@ -152,15 +158,15 @@ __global__ __launch_bounds__(64 * FIN_WAVES) void k_decide_finalize(DecideParams
     }
     count += __popcll(bal);
   }
-  if (lane == 0) out->n_compute = count;
+  if (lane == 0 && host.n_compute) *host.n_compute = count;
 }
 
 hipError_t decide_finalize(const DecideParams& p, const double* partials, const uint8_t* ovr,
-                           double* a, uint8_t* has_ref, uint8_t* mask, double* a_seen,
-                           int32_t* slots, int32_t* branch, DecideOut* out, hipStream_t st) {
+                           double* a, uint8_t* has_ref, uint8_t* mask, int32_t* slots, int32_t* branch,
+                           const DecideHost& host, hipStream_t st) {
   if (p.n_streams > MAX_DECIDE_STREAMS) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_decide_finalize, dim3(1), dim3(64 * FIN_WAVES), 0, st, p, partials, ovr, a, has_ref,
-                     mask, a_seen, slots, branch, out);
+                     mask, slots, branch, host);
   return hipGetLastError();
 }
 

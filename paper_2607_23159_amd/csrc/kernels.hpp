@@ -96,16 +96,20 @@ template <typename T>
 hipError_t residual_add(float* z, const T* y, const float* gate, long rows, int d, hipStream_t st);
 
 // ---- cache rule, update, score (k_cache.hip)
-struct DecideOut {     // written by the decision kernel, read back by the host
-  int32_t n_compute;
-  int32_t pad;
+// Pinned host memory (device addresses) for the decision's result; n_compute
+// NULL: the host knows it already.
+struct DecideHost {
+  int32_t* n_compute;
+  uint8_t* mask;
+  double* a_seen;
 };
 // Partial sums per (candidate, branch, chunk): sum (x - xref)^2 and sum xref^2.
 int decide_chunks(long D);
 hipError_t decide_partials(const float* x, const float* xref, int n_cand, int n_branch, long D,
                            double* partials, hipStream_t st);
-// Finalize: per stream s = i*B + b, forced / rule / override -> mask, a_seen,
-// compact list of computed streams and their branches, count.
+// Finalize: per stream s = i*B + b, forced / rule / override -> mask, compact
+// list of computed streams and their branches; mask, indicators and count to
+// the host.
 // Streams (candidates x branches) one decision launch handles: 1024
 // candidates with two branches each.
 constexpr int MAX_DECIDE_STREAMS = 2048;
@@ -115,9 +119,8 @@ struct DecideParams {
   double tau;
 };
 hipError_t decide_finalize(const DecideParams& p, const double* partials, const uint8_t* override_mask,
-                           double* a, uint8_t* has_ref, uint8_t* mask, double* a_seen,
-                           int32_t* slot_list, int32_t* branch_list, DecideOut* out,
-                           hipStream_t st);
+                           double* a, uint8_t* has_ref, uint8_t* mask, int32_t* slot_list,
+                           int32_t* branch_list, const DecideHost& host, hipStream_t st);
 // x_i += dt * cfg(v_i0, v_i1); v_ib = vbuf (computed) or x + delta (skipped);
 // computed streams refresh delta and xref when store_state; the guided
 // velocity is also written to vt_out when it is not NULL.

@@ -288,8 +288,12 @@ struct cs_rollout {
   double *a = nullptr, *partials = nullptr, *spart = nullptr, *scores = nullptr;
   uint8_t *has_ref = nullptr, *ovr = nullptr;
   int32_t *slots = nullptr, *branch = nullptr;
-  char* dec = nullptr;        // device decision block: DecideOut | a_seen[S] | mask[S]
-  char* dec_host = nullptr;   // pinned mirror
+  uint8_t* mask = nullptr;    // decisions of the current step [S]
+  // pinned, written by the decision kernel
+  double* a_seen_host = nullptr;
+  uint8_t* mask_host = nullptr;
+  int32_t* n_compute_host = nullptr;
+  DecideHost dec{};           // their device addresses
   uint8_t* ovr_host = nullptr;  // pinned staging for override masks
   double* scores_host = nullptr;
   Workspace ws;
@@ -304,11 +308,6 @@ struct cs_rollout {
   long long self_reused = 0, cross_reused = 0;
   std::vector<uint8_t> has_ref_h;
   long long calls = 0, computed = 0;
-  size_t dec_bytes() const { return sizeof(DecideOut) + (size_t)S * sizeof(double) + (size_t)S; }
-  double* a_seen_dev() { return reinterpret_cast<double*>(dec + sizeof(DecideOut)); }
-  uint8_t* mask_dev() { return reinterpret_cast<uint8_t*>(dec + sizeof(DecideOut) + (size_t)S * sizeof(double)); }
-  const double* a_seen_h() const { return reinterpret_cast<const double*>(dec_host + sizeof(DecideOut)); }
-  const uint8_t* mask_h() const { return reinterpret_cast<const uint8_t*>(dec_host + sizeof(DecideOut) + (size_t)S * sizeof(double)); }
   ~cs_rollout() {
     if (vtil) hipFree(vtil);
     if (arena) hipFree(arena);
@@ -813,7 +812,7 @@ static void rollout_layout(cs_rollout* r, Layout& l) {
   l.take(r->ovr, S);
   l.take(r->slots, S * sizeof(int32_t));
   l.take(r->branch, S * sizeof(int32_t));
-  l.take(r->dec, r->dec_bytes());
+  l.take(r->mask, S);
   ws_layout(m, r->ws, (int)S, l);
   ctx_layout(m, r->ctx, r->desc.n_branch, l);
   if (r->desc.mode == CS_CACHE_PAB) {
@@ -824,7 +823,9 @@ static void rollout_layout(cs_rollout* r, Layout& l) {
 }
 
 static void rollout_host_layout(cs_rollout* r, Layout& l) {
-  l.take(r->dec_host, r->dec_bytes());
+  l.take(r->a_seen_host, (size_t)r->S * sizeof(double));
+  l.take(r->mask_host, (size_t)r->S);
+  l.take(r->n_compute_host, sizeof(int32_t));
   l.take(r->ovr_host, (size_t)r->S);
   l.take(r->scores_host, r->desc.n_cand * sizeof(double));
 }
@@ -860,6 +861,9 @@ static cs_status rollout_init_impl(cs_model* m, const cs_rollout_desc* desc, con
     HIPC(hipHostMalloc(&r->host_arena, h.bytes, hipHostMallocDefault));
     h = Layout{(char*)r->host_arena, 0};
     rollout_host_layout(r.get(), h);
+    HIPC(hipHostGetDevicePointer((void**)&r->dec.n_compute, r->n_compute_host, 0));
+    HIPC(hipHostGetDevicePointer((void**)&r->dec.mask, r->mask_host, 0));
+    HIPC(hipHostGetDevicePointer((void**)&r->dec.a_seen, r->a_seen_host, 0));
   }
   TRY(ws_clear(m, r->ws));
   TRY(ctx_clear(m, r->ctx));
@@ -916,6 +920,13 @@ static cs_status decide_impl(cs_rollout* r, int32_t step, const uint8_t* ovr, ui
   bool any_ref = false;
   for (uint8_t h : r->has_ref_h) any_ref |= h != 0;
   const bool need_partials = d.mode == CS_CACHE_ADAPTIVE && !window_forced && any_ref;
+  // Without the drift rule the decision follows from the step number and from
+  // which streams have a residual, all known here: the device takes the same
+  // one for its own lists, and without host outputs (which promise a wait)
+  // nothing is waited for, so that the host runs ahead.  (An override waits:
+  // its staging buffer is reused by the next step.)
+  const bool host_knows = !need_partials && !ovr;
+  DecideParams p;
   {
     ProfScope ps(m->prof, CS_K_DECIDE, st);
     if (need_partials)
@@ -924,21 +935,30 @@ static cs_status decide_impl(cs_rollout* r, int32_t step, const uint8_t* ovr, ui
       memcpy(r->ovr_host, ovr, r->S);
       HIPC(hipMemcpyAsync(r->ovr, r->ovr_host, r->S, hipMemcpyHostToDevice, st));
     }
-    DecideParams p;
     p.n_streams = r->S; p.n_branch = d.n_branch; p.step = step; p.n_steps = d.n_steps;
     p.k_warm = d.k_warm; p.k_cool = d.k_cool; p.mode = d.mode; p.static_k = std::max(1, d.static_k);
     p.nchunk = r->nchunk; p.use_partials = need_partials ? 1 : 0; p.use_override = ovr ? 1 : 0;
     p.tau = (double)d.tau;
-    HIPC(decide_finalize(p, r->partials, r->ovr, r->a, r->has_ref, r->mask_dev(), r->a_seen_dev(),
-                         r->slots, r->branch, reinterpret_cast<DecideOut*>(r->dec), st));
+    HIPC(decide_finalize(p, r->partials, r->ovr, r->a, r->has_ref, r->mask, r->slots, r->branch,
+                         host_knows ? DecideHost{} : r->dec, st));
   }
-  HIPC(hipMemcpyAsync(r->dec_host, r->dec, r->dec_bytes(), hipMemcpyDeviceToHost, st));
-  HIPC(hipStreamSynchronize(st));
-  r->n_compute = reinterpret_cast<const DecideOut*>(r->dec_host)->n_compute;
-  const uint8_t* mk = r->mask_h();
-  for (int s = 0; s < r->S; ++s) if (mk[s]) r->has_ref_h[s] = 1;
-  if (mask_out) memcpy(mask_out, mk, r->S);
-  if (a_out) memcpy(a_out, r->a_seen_h(), r->S * sizeof(double));
+  if (host_knows) {
+    r->n_compute = 0;
+    for (int s = 0; s < r->S; ++s) {
+      const bool forced = window_forced || d.mode == CS_CACHE_OFF || !r->has_ref_h[s];
+      const bool compute = forced || d.mode != CS_CACHE_STATIC || (step - d.k_warm) % p.static_k == 0;
+      r->mask_host[s] = compute ? 1 : 0;
+      r->a_seen_host[s] = NAN;
+      r->n_compute += compute;
+    }
+    if (mask_out || a_out) HIPC(hipStreamSynchronize(st));
+  } else {
+    HIPC(hipStreamSynchronize(st));
+    r->n_compute = *r->n_compute_host;
+  }
+  for (int s = 0; s < r->S; ++s) if (r->mask_host[s]) r->has_ref_h[s] = 1;
+  if (mask_out) memcpy(mask_out, r->mask_host, r->S);
+  if (a_out) memcpy(a_out, r->a_seen_host, r->S * sizeof(double));
   r->decided_step = step;
   return CS_OK;
 }
@@ -980,7 +1000,7 @@ static cs_status step_impl(cs_rollout* r, int32_t step) {
     ProfScope ps(m->prof, CS_K_UPDATE, st);
     const float dt = r->t[step] - r->t[step - 1];
     const int store_state = d.mode == CS_CACHE_ADAPTIVE || d.mode == CS_CACHE_STATIC;
-    HIPC(cache_update(r->x, r->xref, r->delta, r->vbuf, r->mask_dev(), d.n_cand, d.n_branch, r->D, dt,
+    HIPC(cache_update(r->x, r->xref, r->delta, r->vbuf, r->mask, d.n_cand, d.n_branch, r->D, dt,
                       d.guidance, store_state, r->vtil, st));
     if (r->vtil) r->vtil_step = step;
   }
