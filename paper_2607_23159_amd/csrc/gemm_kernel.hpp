@@ -133,9 +133,9 @@ CS_DEV void gemm_tile_of(int tiles_m, int tiles_n, int& tm_i, int& tn_i) {
 }
 
 // ---------------------------------------------------------------------------
-// bf16 GEMM, 4 waves of (BM/2) x (BN/2): one wave per SIMD at BM x BN = 256 x
-// 256 and 192 x 256, two workgroups per CU (OCC = 2) at 128 x 128 and three at
-// 64 x 64; the accumulators are held in AGPRs.
+// bf16 GEMM, 4 waves of (BM/2) x (BN/2): one wave per SIMD at BN = 256 (BM =
+// 256, 224, 192, 160), two workgroups per CU (OCC = 2) at 128 x 128 and three
+// at 64 x 64; the accumulators are held in AGPRs.
 //
 // Fragment reads from LDS per product: (BM/32 + 8) reads per BM/4 products,
 // against 12 per 32 with 8 waves of 128x64, so the LDS, which also absorbs
@@ -666,7 +666,7 @@ template <typename T> struct EpiQKV {
           stage[(16 * j + 4 * (lane >> 4) + r) * SP + 16 * i + (lane & 15)] = to_t<T>(acc[i][j][r]);
     __syncthreads();
     // lane: tokens row0..row0+7 of channels c = CPI*q + lane / CHUNKS (with 96
-    // rows, 12 chunks, the last 4 lanes have none)
+    // rows, 12 chunks, the last 4 lanes have none; likewise 80 and 112 rows)
     constexpr int CPI = 64 / CHUNKS;
     if (lane >= CPI * CHUNKS) return;
     const int k = lane % CHUNKS;

@@ -54,7 +54,7 @@ template <class Epi> struct EpiIsResidual : std::false_type {};
 template <int G> struct EpiIsResidual<EpiResidual<G>> : std::true_type {};
 template <int G, typename T> struct EpiIsResidual<EpiResidualStore<G, T>> : std::true_type {};
 enum Bf16Tile {
-  W4_256x256, W4_192x256, W4_128x128, W4_64x64,
+  W4_256x256, W4_224x256, W4_192x256, W4_160x256, W4_128x128, W4_64x64,
   RING_128x128, RING_64x128, RING_64x64, RING_32x64, RING_32x32, N_TILES
 };
 
@@ -64,33 +64,31 @@ enum Bf16Tile {
 // filled part of the last round (left out when 0), `lone` and `full` are the
 // time per K slice of 64 of a tile alone on its CU and of a full chip, and epi
 // grows by epi_res for residual updates.  The constants are a least-squares fit
-// to 697 measured shapes (32 to 12,480 rows; N and K of projections at widths
+// to 966 measured shapes (32 to 65,520 rows; N and K of projections at widths
 // 128 to 5120 and of the heads; bf16 stores and residual updates), each launch
 // on another copy of the weights out of 900 MB: in a model a layer's weights
 // come from HBM, which shifts the choice towards shapes with more loads in
 // flight.  They were then adjusted for the choice rather than for the times:
-// it costs 1.0% on average over the 697 (at most 20%, at launches of 20 us)
-// against the best tile of each, where 256 x 256 tiles for everything took 3.2
-// times as long on average.
+// against the best tile of each shape it costs 1.0% on average below 1,024 rows
+// or so (at most 20%, at launches of 20 us) and 0.6% above, where 256 x 256
+// tiles for everything took 3.2 times and 12% longer on average.  The row counts
+// between 128 and 256 are for the last round: 12,480 x 1536 x 8960 takes 384 us
+// with 256 rows (294 workgroups on 256 CUs), 315 with 192 and 297 with 160 (468,
+// two nearly full rounds), 12,480 x 4608 x 1536 154 us with 256 and 144 with 224.
 struct TileCost { int bm, bn, slots; double lone, full, fixed, epi, epi_res; };
 static const TileCost TILE_COST[N_TILES] = {
-    {256, 256, 1, 0.879, 1.136, 3.65, 7.42, 18.9},
-    {192, 256, 1, 0.947, 1.053, 3.05, 5.59, 10.2},
-    {128, 128, 2, 0.523, 0.864, 1.51, 3.36, 4.13},
-    {64, 64, 3, 0.355, 0.561, 1.53, 1.15, 1.00},
-    {128, 128, 1, 0.343, 0.464, 1.73, 3.59, 2.69},
-    {64, 128, 1, 0.331, 0.349, 1.78, 2.24, 1.11},
-    {64, 64, 1, 0.200, 0.222, 1.80, 1.54, 0.38},
-    {32, 64, 2, 0.166, 0.285, 1.77, 1.07, 0.25},
-    {32, 32, 2, 0.167, 0.238, 1.72, 0.77, 0.00},
+    {256, 256, 1, 1.022, 1.378, 3.20, 6.88, 16.20},
+    {224, 256, 1, 0.820, 1.222, 1.71, 6.29, 14.71},
+    {192, 256, 1, 0.785, 1.107, 3.09, 5.48, 11.52},
+    {160, 256, 1, 0.754, 0.977, 1.74, 3.78, 9.75},
+    {128, 128, 2, 0.472, 0.930, 2.00, 2.62, 5.00},
+    {64, 64, 3, 0.246, 0.646, 2.07, 1.14, 0.88},
+    {128, 128, 1, 0.469, 0.457, 1.29, 4.23, 2.50},
+    {64, 128, 1, 0.355, 0.368, 1.56, 2.16, 0.92},
+    {64, 64, 1, 0.198, 0.218, 1.79, 1.51, 0.41},
+    {32, 64, 2, 0.164, 0.276, 1.86, 1.05, 0.25},
+    {32, 32, 2, 0.159, 0.245, 1.76, 0.76, 0.00},
 };
-// From two rounds of 256 x 256 tiles on, the chip's power limit evens out a
-// partly filled last round (idle CUs let the others clock higher), so only 192
-// x 256 competes, and only with 3% in hand: 43,680 x 3072 x 3072 (8.02 rounds)
-// takes 775 us with 192 rows against 819, but 262,080 rows (24 rounds) 1% more.
-// Narrow outputs (the head) would leave most of a 256-wide tile empty.
-constexpr long LARGE_TILES = 512, LARGE_MIN_N = 1024;
-constexpr double LARGE_MARGIN = 0.97;
 
 static Bf16Tile choose_tile(long M, long N, long K, long batch, bool residual) {
   const double nk = (double)(K / SLICE_K<bf16>);
@@ -102,9 +100,6 @@ static Bf16Tile choose_tile(long M, long N, long K, long batch, bool residual) {
     if (r > 0) t += nk * (c.lone + (c.full - c.lone) * r) + epi * 0.5 * (1.0 + r);
     return t;
   };
-  const long tiles256 = (long)cdiv(M, 256) * cdiv(N, 256) * batch;
-  if (tiles256 >= LARGE_TILES && N >= LARGE_MIN_N)
-    return cost(W4_192x256) < LARGE_MARGIN * cost(W4_256x256) ? W4_192x256 : W4_256x256;
   int best = W4_256x256;
   double best_t = cost(best);
   for (int i = 0; i < N_TILES; ++i) {
@@ -153,6 +148,8 @@ static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, 
     constexpr int PD = RES ? 8 : 2, PD2 = RES ? 4 : 2;
     switch (choose_tile(M, N, K, b.n, RES)) {
       case W4_256x256: launch_w4<256, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
+      case W4_224x256: launch_w4<224, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
+      case W4_160x256: launch_w4<160, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
       case W4_192x256: launch_w4<192, 256, 1, PD>(A, lda, W, M, N, K, b, epi, st); break;
       case W4_128x128: launch_w4<128, 128, 2, PD2>(A, lda, W, M, N, K, b, epi, st); break;
       case W4_64x64: launch_w4<64, 64, 3, 2>(A, lda, W, M, N, K, b, epi, st); break;
