@@ -423,11 +423,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __re
   gemm_tile_of<GM>(tiles_m, tiles_n, tm_i, tn_i);
   const int m0 = tm_i * BM, n0 = tn_i * BN;
 
-  // operand ranges and per-lane offsets as in k_gemm_w4
+  // per-lane offsets as in k_gemm_w4; the bases move from slice to slice, so
+  // that the 32-bit ranges cover one slice: the tile's rows of A up to its end,
+  // and the tile's part of a W block
   const T* a_base = A + (long)m0 * lda;
   const int n_in = n0 % W_BLOCK_ROWS;
   const T* b_base = W + (long)(n0 - n_in) * K + n_in * BK;
-  const int a_bytes = min(BM, M - m0) * (int)lda * ES, b_bytes = (W_BLOCK_ROWS * K - n_in * BK) * ES;
+  const int a_bytes = ((min(BM, M - m0) - 1) * (int)lda + BK) * ES, b_bytes = BN * BK * ES;
   int a_off[A_INST], b_off[B_INST];
 #pragma unroll
   for (int i = 0; i < A_INST; ++i) {
@@ -447,11 +449,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __re
       const int slice = min(step * SL + l, nslice - 1);
 #pragma unroll
       for (int i = 0; i < A_INST; ++i)
-        buffer_load_lds16(a_base, a_bytes, sa + (wave * A_INST + i) * RPI * BK, a_off[i], slice * BK * ES);
+        buffer_load_lds16(a_base + (long)slice * BK, a_bytes, sa + (wave * A_INST + i) * RPI * BK, a_off[i], 0);
 #pragma unroll
       for (int i = 0; i < B_INST; ++i)
-        buffer_load_lds16(b_base, b_bytes, sb + (wave * B_INST + i) * RPI * BK, b_off[i],
-                          slice * W_BLOCK_ROWS * BK * ES);
+        buffer_load_lds16(b_base + (long)slice * W_BLOCK_ROWS * BK, b_bytes,
+                          sb + (wave * B_INST + i) * RPI * BK, b_off[i], 0);
     }
   };
 

@@ -142,8 +142,10 @@ static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, 
   if (M <= 0 || N <= 0) return hipSuccess;
   if (b.n < 1 || b.n > MAX_BATCH || (b.n > 1 && !EpiBatched<Epi>::value)) return hipErrorInvalidValue;
   if (K <= 0 || K % SLICE_K<T> != 0 || N % 4 != 0) return hipErrorInvalidValue;
-  // per-tile buffer ranges are 32-bit byte counts
-  if ((long)W_BLOCK_ROWS * std::max(lda, (long)K) * (long)sizeof(T) > 0x7FFFFFFFL) return hipErrorInvalidValue;
+  // buffer ranges are 32-bit byte counts: k_gemm_w4's of a whole W block row,
+  // k_gemm_ring's of a tile's rows of A
+  const long row_bytes = std::max(lda, (long)K) * (long)sizeof(T);
+  if ((sizeof(T) == 2 ? W_BLOCK_ROWS : 32) * row_bytes > 0x7FFFFFFFL) return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 2) {
     constexpr bool RES = EpiIsResidual<Epi>::value;
     // residual operands in flight per wave: with one wave per SIMD nothing
@@ -163,7 +165,7 @@ static hipError_t launch(const T* A, long lda, const T* W, int M, int N, int K, 
       default: launch_ring<T, 32, 32, 2, 2, 2, 4, 2>(A, lda, W, M, N, K, b, epi, st);
     }
   } else {
-    if ((long)cdiv(M, 64) * cdiv(N, 64) * b.n >= F32_64_TILES)
+    if ((long)cdiv(M, 64) * cdiv(N, 64) * b.n >= F32_64_TILES && 64 * row_bytes <= 0x7FFFFFFFL)
       launch_ring<T, 64, 64, 2, 4, 2, 2, 4>(A, lda, W, M, N, K, b, epi, st);
     else
       launch_ring<T, 32, 32, 2, 2, 2, 2, 4>(A, lda, W, M, N, K, b, epi, st);
