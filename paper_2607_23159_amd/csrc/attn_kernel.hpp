@@ -519,6 +519,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
   const int head = hs % a.heads, s = hs / a.heads;
   const int kvs = a.kv_sel ? a.kv_sel[s] : s;
   const int q0 = qt * (NW * 32) + wave * 32;
+  // With 12 waves, a wave past the last query only loads: a head's last tile has
+  // up to 11 of them (8 x 1,560 tokens: 153 -> 145 us, 4 x 3,120: 255 -> 248 us,
+  // 27,280 tokens: 1%).  With 8 and 4 waves the branch in the key loop costs the
+  // full tiles more (1.4% and 4%) than the few idle waves take.
+  const bool active = NW < 12 || q0 < a.lq;
 
   const bf16* qb_ = a.q + (long)s * a.q_ss + head * DH;
   const bf16* kb_ = a.k + (long)kvs * a.k_ss + head * DH;
@@ -602,6 +607,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
       else wait_vm_barrier<0>();
     }
     if (t + STAGES - 1 < ntiles) issue(t + STAGES - 1, (t + STAGES - 1) % STAGES);
+    if (NW >= 12 && !active) continue;
     const char* pk = smem + (t % STAGES) * STAGE + lane_k;
     const char* pv = smem + (t % STAGES) * STAGE + lane_v;
     const int kv0 = t * KVT;
