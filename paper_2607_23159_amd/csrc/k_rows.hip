@@ -4,6 +4,8 @@
 // over the row in a fixed lane/step order.
 #include "kernels.hpp"
 
+#include <type_traits>
+
 namespace cs {
 
 // ---------------------------------------------------------------- layer norm
@@ -296,13 +298,21 @@ hipError_t patchify(const float* x, const int* slot_id, int n_slots, int cand_di
 // each product's epilogue does what follows it.
 //
 // Bound by reading the weights once (mod_w: 28 MB at d = 1536, 315 MB at d =
-// 5120).  A wave takes GEMV_ROWS rows at a time, 16 bytes per lane and row, so
-// that GEMV_ROWS x K/512 loads are in flight; the input vector is shared by the
-// rows and comes from L2.  Measured for the three together (features, products
-// and tables): 58 -> 18 us at d = 1536, 270 -> 83 us at d = 5120 (mod_w at 5.0
-// TB/s), where 2-byte loads of one row per wave and five launches took the
-// former.
-constexpr int GEMV_ROWS = 4, GEMV_WAVES = 4;
+// 5120).  Every sum has one fixed order, whatever the layout below: 64 partial
+// sums, sum c over the columns k = c mod 64 in increasing k (fused
+// multiply-adds), added in halves (c and c + 32, then 16, 8, 4, 2, 1).  A bf16
+// evaluation turns a last-bit change of a modulation vector into some 0.2% of
+// its output, through the roundings that follow, so the order is part of the
+// result.
+//
+// A wave takes GEMV_ROWS rows: eight lanes per row, eight consecutive columns
+// (partial sums) each, so that a step reads 16 bytes per lane, one whole line
+// of each row in bf16, and eight to sixteen steps are in flight.  The input vector
+// is shared by the rows: a wave brings 512 columns at a time into LDS.  Measured
+// for the three launches together (features, products and tables): 58 -> 18 us
+// at d = 1536, 270 -> 76 us at d = 5120 (mod_w at 5.4 TB/s), where 2-byte loads
+// of one row per wave, in the same order, and five launches took the former.
+constexpr int GEMV_ROWS = 8, GEMV_WAVES = 4;
 enum TimeStage { TIME_HIDDEN = 0, TIME_EMBED = 1, TIME_MOD = 2 };
 
 // Sinusoidal timestep features [cos(1000 t w_k), sin(1000 t w_k)], w_k =
@@ -317,54 +327,128 @@ CS_DEV void time_features(float t, int half, float* out) {
   }
 }
 
+// U steps of 64 columns of a lane's row.  load() only requests them: the
+// memory clobber keeps the compiler from sinking each load to its use, which
+// leaves one or two in flight (41 us for the three launches at d = 1536).
+template <typename T, int U> struct GemvTile {
+  typedef typename std::conditional<sizeof(T) == 2, bf16x8, f32x4>::type chunk;
+  static constexpr int NC = 8 * (int)sizeof(T) / 16, CE = 8 / NC;   // chunks per step, elements per chunk
+  chunk c[U][NC];
+  CS_DEV void load(const T* w) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < NC; ++j) c[u][j] = *reinterpret_cast<const chunk*>(w + 64 * u + CE * j);
+    asm volatile("" ::: "memory");
+  }
+  // x: the tile's columns of the input vector, from this lane's first on (LDS)
+  CS_DEV void mul(const float* x, float (&s)[8]) const {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float xv[8];
+      Vec8<float>::get(x + 64 * u, xv);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s[i] = fmaf(to_f(c[u][i / CE][i % CE]), xv[i], s[i]);
+    }
+  }
+};
+
 template <typename T, int STAGE>
 __global__ __launch_bounds__(64 * GEMV_WAVES) void k_time_cond(const T* __restrict__ W, const float* __restrict__ b,
                                                                const float* __restrict__ x, int N, int K,
                                                                float t, float* __restrict__ act,
                                                                const float* __restrict__ tables, int n_tables,
                                                                float* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) float feat[STAGE == TIME_HIDDEN ? 256 : 4];
+  // the features, or a wave's 512 columns of x
+  constexpr int COLS = 512;
+  __shared__ __attribute__((aligned(16))) float sx[GEMV_WAVES][COLS];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane & 7;
+  const int n0 = (blockIdx.x * GEMV_WAVES + wave) * GEMV_ROWS;
+  const int n = min(n0 + (lane >> 3), N - 1);
+  const T* wr = W + (long)n * K + 8 * q;
+  float s[8] = {};   // partial sums 8 q + i
   if constexpr (STAGE == TIME_HIDDEN) {
-    time_features(t, K / 2, feat);
+    GemvTile<T, 4> w;   // K = 256
+    w.load(wr);
+    time_features(t, K / 2, sx[0]);
     __syncthreads();
-    x = feat;
-  }
-  const int lane = threadIdx.x & 63;
-  const int n0 = (blockIdx.x * GEMV_WAVES + (threadIdx.x >> 6)) * GEMV_ROWS;
-  if (n0 >= N) return;
-  const T* wr = W + (long)n0 * K;
-  float s[GEMV_ROWS] = {};
-  for (int k = lane * 8; k < K; k += 512) {
+    w.mul(sx[0] + 8 * q, s);
+  } else {
+    // columns [k, k + cols) of x through LDS: each lane brings eight of them
+    // (the wave's own region, so no barrier: its LDS accesses run in order)
+    float* const xw = sx[wave];
     float xv[8];
-    Vec8<float>::get(x + k, xv);
-#pragma unroll
-    for (int r = 0; r < GEMV_ROWS; ++r) {
-      float wv[8];
-      Vec8<T>::get(wr + (long)r * K + k, wv);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) s[r] += wv[i] * xv[i];
+    auto get_x = [&](int k, int cols) { if (8 * lane < cols) Vec8<float>::get(x + k + 8 * lane, xv); };
+    auto put_x = [&](int cols) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (8 * lane < cols) Vec8<float>::put(xw + 8 * lane, xv);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    auto tail = [&](auto steps, int k) {
+      constexpr int U = decltype(steps)::value;
+      GemvTile<T, U> w;
+      get_x(k, 64 * U);
+      w.load(wr + k);
+      put_x(64 * U);
+      w.mul(xw + 8 * q, s);
+    };
+    int k = 0;
+    // Two tiles in turn, one in flight while the other is multiplied.  Whether a
+    // step requests the next tile is fixed at compile time: behind a run-time
+    // branch the compiler waits for that tile as well.
+    if (K >= COLS) {
+      typedef std::integral_constant<bool, true> More;
+      typedef std::integral_constant<bool, false> Last;
+      GemvTile<T, 8> w0, w1;
+      get_x(0, COLS);
+      w0.load(wr);
+      auto step = [&](GemvTile<T, 8>& cur, GemvTile<T, 8>& nxt, auto more) {
+        put_x(COLS);
+        if constexpr (decltype(more)::value) {
+          get_x(k + COLS, COLS);
+          nxt.load(wr + k + COLS);
+        }
+        cur.mul(xw + 8 * q, s);
+        k += COLS;
+      };
+      while (k + 3 * COLS <= K) {
+        step(w0, w1, More());
+        step(w1, w0, More());
+      }
+      if (k + 2 * COLS <= K) {
+        step(w0, w1, More());
+        step(w1, w0, Last());
+      } else {
+        step(w0, w1, Last());
+      }
     }
+    if (K & 256) { tail(std::integral_constant<int, 4>(), k); k += 256; }
+    if (K & 128) { tail(std::integral_constant<int, 2>(), k); k += 128; }
+    if (K & 64) tail(std::integral_constant<int, 1>(), k);
   }
-  const float4 bv = *reinterpret_cast<const float4*>(b + n0);
-  const float4 y = make_float4(wave_sum(s[0]) + bv.x, wave_sum(s[1]) + bv.y, wave_sum(s[2]) + bv.z,
-                               wave_sum(s[3]) + bv.w);
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1)   // partial sums 32, 16 and 8 apart
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] += __shfl_xor(s[i], o, WAVE);
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1)   // 4, 2 and 1 apart
+#pragma unroll
+    for (int i = 0; i < o; ++i) s[i] += s[i + o];
+  if (n0 >= N) return;
+  const float y = s[0] + b[n];
   if constexpr (STAGE != TIME_MOD) {
-    if (lane == 0)
-      *reinterpret_cast<float4*>(act + n0) = make_float4(silu(y.x), silu(y.y), silu(y.z), silu(y.w));
+    if (q == 0) act[n] = silu(y);
   }
   if constexpr (STAGE != TIME_HIDDEN) {
-    for (int j = lane; j < n_tables; j += 64) {
-      const float4 p = *reinterpret_cast<const float4*>(tables + (long)j * N + n0);
-      *reinterpret_cast<float4*>(out + (long)j * N + n0) = make_float4(y.x + p.x, y.y + p.y, y.z + p.z, y.w + p.w);
-    }
+    for (int j = q; j < n_tables; j += 8) out[(long)j * N + n] = y + tables[(long)j * N + n];
   }
 }
 
 template <typename T>
 hipError_t time_conditioning(const TimeCond<T>& c, float t, hipStream_t st) {
   const int d = c.d;
-  // 16-byte accesses along rows and outputs; the features fill 256 floats
-  if (d % 8 != 0 || c.freq_dim != 256) return hipErrorInvalidValue;
+  // steps of 64 columns, waves of whole rows; the features fill 256 floats
+  if (d % 64 != 0 || c.freq_dim != 256) return hipErrorInvalidValue;
   auto grid = [](int n) { return dim3((unsigned)cdiv(n, GEMV_ROWS * GEMV_WAVES)); };
   const dim3 block(64 * GEMV_WAVES);
   hipLaunchKernelGGL((k_time_cond<T, TIME_HIDDEN>), grid(d), block, 0, st, c.w1, c.b1, (const float*)nullptr, d,
