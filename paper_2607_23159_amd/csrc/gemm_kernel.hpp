@@ -413,7 +413,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __re
   static_assert(A_INST * RPI * NWAVE == BM && B_INST * RPI * NWAVE == BN, "load split");
   static_assert(W_BLOCK_ROWS % BN == 0, "part of a tiled W block");
   static_assert(STAGES >= 2 && STAGES <= 4, "wait counts below");
-  __shared__ __attribute__((aligned(1024))) T smem[STAGES * STAGE];
+  // the ring, then 1 KB of bias per wave.  One array: the compiler waits for all
+  // direct loads before a read of a second one.
+  __shared__ __attribute__((aligned(1024))) T smem[STAGES * STAGE + NWAVE * 1024 / ES];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform
@@ -457,8 +459,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __re
     }
   };
 
-  f32x4 acc[TM][TN];
-  init_acc16_bias(acc, epi.bias, n0 + wn * WN, lane, N);
+  // The bias from the wave's first column on (zeros past N) comes in by the first
+  // of the direct loads: the wait for step 0 covers it.  A load into registers
+  // would be waited for by the compiler, which cannot count the conditional loads
+  // behind it and waits for all of them, the whole ring, before the first product.
+  T* const s_bias = smem + STAGES * STAGE + wave * (1024 / ES);
+  buffer_load_lds16(epi.bias, N * 4, s_bias, (n0 + wn * WN) * 4 + lane * 16, 0);
 
 #pragma unroll
   for (int s = 0; s < STAGES; ++s)
@@ -481,6 +487,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __re
       for (int i = 0; i < TM; ++i) o[ks][i] = *reinterpret_cast<const chunk*>(s + a_lds[ks & 1] + i * 16 * BK);
     }
   };
+  if (nstep >= STAGES) wait_all_barrier<(STAGES - 1) * PER>();   // bias and step 0 landed
+  else wait_all_barrier<0>();
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      acc[i][j] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(s_bias) + 16 * j + 4 * (lane >> 4));
+  read(0, f[0]);
   auto mul = [&](int step, const chunk(&o)[2 * SL][NF]) {
 #pragma unroll
     for (int ks = 0; ks < 2 * SL; ++ks) {
@@ -492,9 +507,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void k_gemm_ring(const T* __re
           acc[i][j] = Mfma16<T>::mma(o[ks][TM + j], o[ks][i], acc[i][j]);
     }
   };
-  if (nstep >= STAGES) wait_all_barrier<(STAGES - 1) * PER>();   // step 0 landed
-  else wait_all_barrier<0>();
-  read(0, f[0]);
   // step k: products of k from registers `cur`, reads of k+1 into `nxt`
   auto step = [&](int k, const chunk(&cur)[2 * SL][NF], chunk(&nxt)[2 * SL][NF]) {
     if (k + 1 < nstep) {
