@@ -249,11 +249,14 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_dl(AttnArgs<bf16> a) {
     const int row = min(q0 + qb * 32 + l32, a.lq - 1);
     const bf16* src = qb_ + (long)row * a.q_ld + MF::KPL * half;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      qf[qb][ks] = MF::load(src + ks * KSTEP);
-      asm volatile("" : "+v"(qf[qb][ks]));
-    }
+    for (int ks = 0; ks < NKS; ++ks) qf[qb][ks] = MF::load(src + ks * KSTEP);
   }
+  // all requested before the first is waited for, and waited for before the
+  // direct loads, which are counted
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[qb][ks]));
 
   // per-lane load sources: lane covers row (lane / CPR) of its instruction's
   // rows and physical chunk lane % CPR, i.e. logical chunk phys ^ f(row)
@@ -491,7 +494,10 @@ CS_DEV void store_o_rows(const f32x16 (&o)[NDT], float inv, bf16* dst, int half,
 // waves, one per SIMD, are for grids that leave CUs idle otherwise: 384 tokens
 // x 12 heads 12.4 us against 14.8 with 8 waves and 19.0 with 12.
 //
-// The first tile is requested before Q, so that their latencies overlap.
+// The first tile is requested before Q, and all of Q before any of it is waited
+// for, so that their latencies overlap.  (One wait after each of the eight loads:
+// 40 us for 4 x 32,760 queries, 4 x 64 heads and 19 keys, 34.5 without; longer key
+// loops do not show it.)
 // ---------------------------------------------------------------------------
 template <int DH, int NW, int OCC, int STAGES, bool EARLY, bool CROSS>
 __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
@@ -578,10 +584,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_pad(AttnArgs<bf16> a) {
     const int row = min(q0 + l32, a.lq - 1);
     const bf16* src = qb_ + (long)row * a.q_ld + MF::KPL * half;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      qf[ks] = MF::load(src + ks * KSTEP);
-      asm volatile("" : "+v"(qf[ks]));
-    }
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = MF::load(src + ks * KSTEP);
+    // all requested before the first is waited for, and waited for before the
+    // direct loads of the later tiles, which are counted
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[ks]));
   }
 #pragma unroll
   for (int t = 1; t < STAGES - 1; ++t)

@@ -66,3 +66,14 @@ def test_ring_gemm_waits_only_at_its_barriers(kernels):
         assert not loads, (name, loads)
         extra = [(i, x) for i, x in enumerate(code[:end]) if _waits_for_loads(x) and code[i + 1] != "s_barrier"]
         assert not extra, (name, extra)
+
+
+@pytest.mark.parametrize("kernel", ["k_flash_pad", "k_flash_dl"])
+def test_attention_requests_all_of_q_before_waiting(kernels, kernel):
+    for name, code in _named(kernels, kernel).items():
+        first = min(i for i, x in enumerate(code) if _is_mfma(x))
+        loads = [i for i, x in enumerate(code[:first]) if _is_register_load(x)]
+        # head_dim / 16 fragments of 16 bytes per lane
+        assert len(loads) >= int(re.search(r"ILi(\d+)E", name).group(1)) // 16, name
+        waits = [x for x in code[loads[0]:loads[-1]] if _waits_for_loads(x)]
+        assert not waits, (name, waits)
