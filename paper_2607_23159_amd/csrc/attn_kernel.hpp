@@ -489,8 +489,11 @@ CS_DEV void store_o_rows(const f32x16 (&o)[NDT], float inv, bf16* dst, int half,
 // softmax: that saves 64 registers and brings a wave to 160, so three waves
 // fit per SIMD, and the third wave hides LDS latency better than early reads
 // (measured 4% faster at 32,760 tokens).  With 8 waves (two per SIMD, 256
-// registers) a tile's K fragments are requested together and its V^T fragments
-// ahead of the softmax (EARLY: 5711 -> 5583 us, one 32,760-token stream).  4
+// registers) and head dim 128 a tile's K fragments are requested together and its
+// V^T fragments ahead of the softmax (EARLY: 5711 -> 5583 us, one 32,760-token
+// stream of 12 heads); at head dim 64, with half the products per tile to cover
+// them, that costs (two 16,384-token streams of 4 heads 555 us without, 580 with,
+// one of 32,760 1101 and 1151).  4
 // waves, one per SIMD, are for grids that leave CUs idle otherwise: 384 tokens
 // x 12 heads 12.4 us against 14.8 with 8 waves and 19.0 with 12.
 //

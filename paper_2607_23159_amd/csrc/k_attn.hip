@@ -97,7 +97,7 @@ static hipError_t launch_flash_pad(const AttnArgs<bf16>& a, hipStream_t st) {
   };
   const double t12 = cost(384, 1.0), t8 = cost(256, 1.06), t4 = cost(128, 1.55);
   if (t4 < t8 && t4 < t12) return launch_flash_pad_nw<DH, 4, 1, 4, false>(a, st);
-  if (t8 < t12) return launch_flash_pad_nw<DH, 8, 2, 3, true>(a, st);
+  if (t8 < t12) return launch_flash_pad_nw<DH, 8, 2, 3, (DH > 64)>(a, st);
   return launch_flash_pad_nw<DH, 12, 3, 3, false>(a, st);
 }
 
