@@ -48,35 +48,47 @@ constexpr float RESCALE_LOG2 = 8.0f;
 // Two streams of 384 tokens, 12 x 128 heads: 46 us (self) and 54 us (512 text
 // keys), against 69 and 87 us with 128-query workgroups staged through LDS; four
 // of 256 tokens, 4 x 32 heads: 7.1 us against 15.6.
+//
+// A fragment load of 32 rows touches 32 lines for 32 bytes each, and at head dims
+// 32 and 64 these loads, not the products, set the pace once the chip is full.
+// There a wave then takes QB = 2 blocks of 32 queries per K and V fragment (each
+// block's arithmetic is the same, so results are bitwise those of QB = 1): 4 x
+// 24,000 tokens, 4 x 64 heads 20.4 -> 18.6 ms, 8 x 16,384 tokens, 4 x 32 heads
+// 10.0 -> 9.0 ms (18.5 and 8.8 with the LDS-staged workgroups).  At head dim 128
+// two blocks do not fit the registers; from some 10,000 queries on the staged
+// workgroups were faster there (32,760 queries: 512 keys 1.00 against 1.20 ms,
+// self 53.9 against 55.3 ms, 2% of it).
 // ---------------------------------------------------------------------------
-template <int DH, int NW, int OCC, bool CROSS>
+template <int DH, int QB, int NW, int OCC, bool CROSS>
 __global__ __launch_bounds__(64 * NW, OCC) void k_flash_f32(AttnArgs<float> a) {
   typedef Mfma32<float> MF;
   constexpr int NG = DH / 8;      // 8-channel groups of the score product
   constexpr int NDT = DH / 32;    // 32-channel blocks of the output
   constexpr int OLD = DH + 4;     // padded row of a partial output
   __shared__ __attribute__((aligned(16))) float s_o[NW][32 * OLD];
-  __shared__ float s_m[NW][32], s_l[NW][32];
+  __shared__ float s_m[QB][NW][32], s_l[QB][NW][32];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, l32 = lane & 31;
-  const int n_qt = (a.lq + 31) / 32;
+  const int n_qt = (a.lq + 32 * QB - 1) / (32 * QB);
   const int vid = xcd_contiguous(blockIdx.x, gridDim.x);
   const int qt = vid % n_qt, hs = vid / n_qt;
   const int head = hs % a.heads, s = hs / a.heads;
   const int kvs = a.kv_sel ? a.kv_sel[s] : s;
-  const int q0 = qt * 32;
+  const int q0 = qt * 32 * QB;
 
   const float* kb_ = a.k + (long)kvs * a.k_ss + head * DH + 4 * half;
   const float* vb_ = a.vt + (long)kvs * a.vt_ss + ((long)head * DH + l32) * a.vt_ld + 4 * half;
 
-  // lane: query l32, channels 8g + 4 half + e in qf[g][e]
-  f32x4 qf[NG];
-  {
-    const float* src = a.q + (long)s * a.q_ss + (long)min(q0 + l32, a.lq - 1) * a.q_ld + head * DH + 4 * half;
+  // lane: query 32 qb + l32, channels 8g + 4 half + e in qf[qb][g][e]
+  f32x4 qf[QB][NG];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) qf[g] = *reinterpret_cast<const f32x4*>(src + 8 * g);
+  for (int qb = 0; qb < QB; ++qb) {
+    const float* src =
+        a.q + (long)s * a.q_ss + (long)min(q0 + 32 * qb + l32, a.lq - 1) * a.q_ld + head * DH + 4 * half;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) qf[qb][g] = *reinterpret_cast<const f32x4*>(src + 8 * g);
   }
   const int nblk = (a.lk + 31) / 32;
   f32x4 kf[NG];
@@ -86,12 +98,17 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_f32(AttnArgs<float> a) {
     for (int g = 0; g < NG; ++g) kf[g] = *reinterpret_cast<const f32x4*>(src + 8 * g);
   };
 
-  f32x16 o[NDT];
+  f32x16 o[QB][NDT];
+  float m_run[QB], l_run[QB];
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
+  for (int qb = 0; qb < QB; ++qb) {
+    m_run[qb] = -INFINITY;
+    l_run[qb] = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
-  float m_run = -INFINITY, l_run = 0.0f;
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[qb][dt][r] = 0.0f;
+  }
 
   if (wave < nblk) load_k(wave);
   for (int blk = wave; blk < nblk; blk += NW) {
@@ -105,49 +122,53 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_f32(AttnArgs<float> a) {
       for (int g = 0; g < 4; ++g)
         vf[dt][g] = *reinterpret_cast<const f32x4*>(vb_ + (long)dt * 32 * a.vt_ld + kv0 + 8 * g);
 
-    // S^T = K Q^T; two chains, so that no product waits for the one before
-    f32x16 sc[2];
+    float p[QB][16];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int qb = 0; qb < QB; ++qb) {
+      // S^T = K Q^T; two chains, so that no product waits for the one before
+      f32x16 sc[2];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sc[c][r] = 0.0f;
+      for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
+        for (int r = 0; r < 16; ++r) sc[c][r] = 0.0f;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sc[e & 1] = MF::mma(kf[g][e], qf[g][e], sc[e & 1]);
-    if (blk + NW < nblk) load_k(blk + NW);
+      for (int g = 0; g < NG; ++g)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      sc[0][r] += sc[1][r];
-      if (kv0 + 32 > a.lk && kv0 + acc_row(r, lane) >= a.lk) sc[0][r] = -INFINITY;
-    }
+        for (int e = 0; e < 4; ++e) sc[e & 1] = MF::mma(kf[g][e], qf[qb][g][e], sc[e & 1]);
+      if (qb == QB - 1 && blk + NW < nblk) load_k(blk + NW);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sc[0][r] += sc[1][r];
+        if (kv0 + 32 > a.lk && kv0 + acc_row(r, lane) >= a.lk) sc[0][r] = -INFINITY;
+      }
 
-    // online softmax.  The running maximum is only raised (and O, l rescaled)
-    // when some lane's block maximum exceeds it by more than RESCALE_LOG2;
-    // otherwise the stale maximum is kept and probabilities may reach
-    // 2^RESCALE_LOG2, which fp32 accumulation carries without loss of relative
-    // precision.  The branch is uniform across the wave.
-    float mx = -INFINITY;
+      // online softmax.  The running maximum is only raised (and O, l rescaled)
+      // when some lane's block maximum exceeds it by more than RESCALE_LOG2;
+      // otherwise the stale maximum is kept and probabilities may reach
+      // 2^RESCALE_LOG2, which fp32 accumulation carries without loss of relative
+      // precision.  The branch is uniform across the wave.
+      float mx = -INFINITY;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[0][r]);
-    mx = max_lane_pair32(mx) * a.scale_log2;
-    if (__any(mx > m_run + RESCALE_LOG2)) {
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-      m_run = m_new;
-      l_run *= alpha;
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[0][r]);
+      mx = max_lane_pair32(mx) * a.scale_log2;
+      if (__any(mx > m_run[qb] + RESCALE_LOG2)) {
+        const float m_new = fmaxf(m_run[qb], mx);
+        const float alpha = __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+        m_run[qb] = m_new;
+        l_run[qb] *= alpha;
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
+        for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+          for (int r = 0; r < 16; ++r) o[qb][dt][r] *= alpha;
+      }
+      float lsum = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        p[qb][r] = __builtin_amdgcn_exp2f(fmaf(sc[0][r], a.scale_log2, -m_run[qb]));
+        lsum += p[qb][r];
+      }
+      l_run[qb] += lsum;
     }
-    float p[16], lsum = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      p[r] = __builtin_amdgcn_exp2f(fmaf(sc[0][r], a.scale_log2, -m_run));
-      lsum += p[r];
-    }
-    l_run += lsum;
 
     // O^T += V^T P^T: register 4g + e of P^T holds key 8g + 4 half + e
 #pragma unroll
@@ -155,40 +176,51 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_flash_f32(AttnArgs<float> a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) o[dt] = MF::mma(vf[dt][g][e], p[4 * g + e], o[dt]);
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+          for (int qb = 0; qb < QB; ++qb) o[qb][dt] = MF::mma(vf[dt][g][e], p[qb][4 * g + e], o[qb][dt]);
   }
 
   // merge: every wave's maximum and sum, then its output scaled to the common
   // maximum (a wave without a block has maximum -inf, sum and output 0)
-  const float l_tot = l_run + __shfl_xor(l_run, 32, WAVE);
-  if (half == 0) {
-    s_m[wave][l32] = m_run;
-    s_l[wave][l32] = l_tot;
-  }
-  __syncthreads();
-  float m_all = s_m[0][l32];
 #pragma unroll
-  for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][l32]);
-  float l_all = 0.0f;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) l_all += s_l[w][l32] * __builtin_amdgcn_exp2f(s_m[w][l32] - m_all);
-  const float f = __builtin_amdgcn_exp2f(m_run - m_all) / l_all;
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 v = {o[dt][4 * g] * f, o[dt][4 * g + 1] * f, o[dt][4 * g + 2] * f, o[dt][4 * g + 3] * f};
-      *reinterpret_cast<f32x4*>(&s_o[wave][l32 * OLD + dt * 32 + 8 * g + 4 * half]) = v;
+  for (int qb = 0; qb < QB; ++qb) {
+    const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32, WAVE);
+    if (half == 0) {
+      s_m[qb][wave][l32] = m_run[qb];
+      s_l[qb][wave][l32] = l_tot;
     }
+  }
   __syncthreads();
   float* dst = a.o + (long)s * a.o_ss + head * DH;
 #pragma unroll
-  for (int i = tid; i < 32 * DH / 4; i += 64 * NW) {
-    const int q = i / (DH / 4), c = 4 * (i % (DH / 4));
-    f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[0][q * OLD + c]);
+  for (int qb = 0; qb < QB; ++qb) {
+    float m_all = s_m[qb][0][l32];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4*>(&s_o[w][q * OLD + c]);
-    if (q0 + q < a.lq) *reinterpret_cast<f32x4*>(dst + (long)(q0 + q) * a.o_ld + c) = v;
+    for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[qb][w][l32]);
+    float l_all = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) l_all += s_l[qb][w][l32] * __builtin_amdgcn_exp2f(s_m[qb][w][l32] - m_all);
+    const float f = __builtin_amdgcn_exp2f(m_run[qb] - m_all) / l_all;
+    if (qb > 0) __syncthreads();   // the previous block's outputs are read
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 v = {o[qb][dt][4 * g] * f, o[qb][dt][4 * g + 1] * f, o[qb][dt][4 * g + 2] * f,
+                         o[qb][dt][4 * g + 3] * f};
+        *reinterpret_cast<f32x4*>(&s_o[wave][l32 * OLD + dt * 32 + 8 * g + 4 * half]) = v;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int i = tid; i < 32 * DH / 4; i += 64 * NW) {
+      const int q = i / (DH / 4), c = 4 * (i % (DH / 4));
+      f32x4 v = *reinterpret_cast<const f32x4*>(&s_o[0][q * OLD + c]);
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4*>(&s_o[w][q * OLD + c]);
+      const int row = q0 + 32 * qb + q;
+      if (row < a.lq) *reinterpret_cast<f32x4*>(dst + (long)row * a.o_ld + c) = v;
+    }
   }
 }
 

@@ -8,20 +8,45 @@ int attn_kv_tile(int dtype_bytes, int head_dim) {
   return head_dim > 64 ? 32 : 64;
 }
 
-// fp32: 32 queries per workgroup, keys split over four waves.
-template <int DH, int OCC>
-static hipError_t launch_flash_f32(const AttnArgs<float>& a, hipStream_t st) {
+static int cu_count() {
+  static int cus[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (!cus[dev]) {
+    int v = 0;
+    cus[dev] = hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0
+                   ? v : 256;
+  }
+  return cus[dev];
+}
+
+// fp32: 32 QB queries per workgroup, keys split over four waves.
+template <int DH, int QB, int OCC>
+static hipError_t launch_flash_f32_qb(const AttnArgs<float>& a, hipStream_t st) {
   constexpr int NW = 4;
-  const long nwg = (long)cdiv(a.lq, 32) * a.heads * a.n_streams;
+  const long nwg = (long)cdiv(a.lq, 32 * QB) * a.heads * a.n_streams;
   if (nwg * 64 * NW > 0xFFFFFFFFL) return hipErrorInvalidConfiguration;
   // 16-byte rows of q, k and o; every 32-key block of V^T inside its padded row
   if (a.q_ld % 4 || a.k_ld % 4 || a.o_ld % 4 || a.vt_ld % 4 || a.vt_ld < round_up(a.lk, 32))
     return hipErrorInvalidValue;
   if (a.kv_sel)
-    hipLaunchKernelGGL((k_flash_f32<DH, NW, OCC, true>), dim3((unsigned)nwg), dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((k_flash_f32<DH, QB, NW, OCC, true>), dim3((unsigned)nwg), dim3(64 * NW), 0, st, a);
   else
-    hipLaunchKernelGGL((k_flash_f32<DH, NW, OCC, false>), dim3((unsigned)nwg), dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((k_flash_f32<DH, QB, NW, OCC, false>), dim3((unsigned)nwg), dim3(64 * NW), 0, st, a);
   return hipGetLastError();
+}
+
+// Head dims 32 and 64: 64 queries per workgroup where that takes less than 1 / 1.85
+// of the rounds of the CUs that 32 take (time of a round 41 and 75 us at head dim 64
+// and 2,048 keys; 4 heads of 1, 2, 3, 4 and 8 streams: 45, 89, 127, 166 and 326 us with
+// 32 queries, 80, 82, 148, 149 and 293 with 64), and the keys are more than one
+// 32-key block per wave.  Results are bitwise the same.
+template <int DH, int OCC1, int OCC2>
+static hipError_t launch_flash_f32(const AttnArgs<float>& a, hipStream_t st) {
+  const long cus = cu_count(), sh = (long)a.heads * a.n_streams;
+  const int r1 = cdiv(cdiv(a.lq, 32) * sh, cus), r2 = cdiv(cdiv(a.lq, 64) * sh, cus);
+  if (a.lk > 128 && 1.85 * r2 < r1) return launch_flash_f32_qb<DH, 2, OCC2>(a, st);
+  return launch_flash_f32_qb<DH, 1, OCC1>(a, st);
 }
 
 // bf16, head dim 32: XOR-swizzled direct-to-LDS tiles of 64 keys in a
@@ -54,18 +79,6 @@ static hipError_t launch_flash_dl(const AttnArgs<bf16>& a, hipStream_t st) {
 // Each wave's arithmetic is the same in all shapes (same key order, same
 // per-wave rescale decisions), so the outputs are bitwise equal and the choice
 // never changes a result.
-static int cu_count() {
-  static int cus[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cus[dev] <= 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cus[dev] = n;
-  }
-  return cus[dev];
-}
-
 template <int DH, int NW, int OCC, int STAGES, bool EARLY>
 static hipError_t launch_flash_pad_nw(const AttnArgs<bf16>& a, hipStream_t st) {
   const long nwg = (long)cdiv(a.lq, NW * 32) * a.heads * a.n_streams;
@@ -116,9 +129,9 @@ template <>
 hipError_t flash_attention<float>(const AttnArgs<float>& a, int head_dim, hipStream_t st) {
   if (a.lq <= 0 || a.n_streams <= 0) return hipSuccess;
   switch (head_dim) {
-    case 128: return launch_flash_f32<128, 1>(a, st);
-    case 64: return launch_flash_f32<64, 2>(a, st);
-    case 32: return launch_flash_f32<32, 4>(a, st);
+    case 128: return launch_flash_f32_qb<128, 1, 1>(a, st);
+    case 64: return launch_flash_f32<64, 2, 2>(a, st);
+    case 32: return launch_flash_f32<32, 4, 3>(a, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -29,6 +29,23 @@ pytestmark = pytest.mark.gpu
     ("wan_mid", (3, 8, 16), (1, 4, 9, 33)),        # 384 rows to 12,672: 64 to 256-row tiles
 ])
 def test_velocity_is_bitwise_the_same_at_every_batch_size(model, grid, batches, dtype):
+    same_at_every_batch_size(model, grid, batches, dtype)
+
+
+# fp32 attention at head dims 32 and 64: one stream takes one block of 32 queries
+# per wave, the batch (512 and 432 workgroups of one block, two rounds of 256 CUs,
+# against one of 64) two.  The last workgroup's second block holds one query (225,
+# 289 tokens) or none (259).
+@pytest.mark.parametrize("model,grid,batches", [
+    ("tiny", (1, 15, 15), (1, 16)),
+    ("tiny", (1, 7, 37), (1, 12)),
+    ("ragged", (1, 17, 17), (1, 12)),
+])
+def test_velocity_with_two_query_blocks_per_wave(model, grid, batches):
+    same_at_every_batch_size(model, grid, batches, synth.DTYPE_FP32)
+
+
+def same_at_every_batch_size(model, grid, batches, dtype):
     import torch
 
     from paper_2607_23159_amd.search import GpuModel
