@@ -323,6 +323,25 @@ def test_static_mode_schedule():
         assert rel_l2(g.latents[i], res.latents[i]) < TOL[1]
 
 
+@pytest.mark.parametrize("n_branch", [1, 2])
+@pytest.mark.parametrize("dtype", [synth.DTYPE_FP32, synth.DTYPE_BF16])
+@pytest.mark.parametrize("mode", [synth.CACHE_OFF, synth.CACHE_STATIC, synth.CACHE_PAB])
+def test_steps_without_host_outputs_take_the_same_decisions(mode, dtype, n_branch):
+    """In the modes whose schedule is fixed, a step that returns no mask waits
+    for nothing: the host forms the decision itself while the device forms its
+    own.  Latents, scores and counts must be those of the rollout that returns
+    every mask, and the counts those of the masks."""
+    gm, m = gpu_model("tiny", dtype, "stress")
+    kw = {"static_k": 3, "k_warm": 2} if mode == synth.CACHE_STATIC else {}
+    wl = synth.make_workload("tiny", dtype=dtype, init="stress", mode=mode, n_branch=n_branch, **kw)
+    a = run_rollout(gm, wl, record=True)
+    b = run_rollout(gm, wl, record=False)
+    assert np.array_equal(a.latents, b.latents) and np.array_equal(a.scores, b.scores)
+    assert (a.computed, a.calls, a.self_reused, a.cross_reused) == (b.computed, b.calls, b.self_reused, b.cross_reused)
+    assert a.computed == a.masks.sum() and np.isnan(a.a).all()
+    assert (a.computed < a.calls) == (mode == synth.CACHE_STATIC)
+
+
 def test_degenerate_schedules():
     """Degenerate settings of the skip rule (Sec. Method, adaptive skip rule
     and its static variant): the static period 1 computes every call and the
