@@ -19,17 +19,33 @@ from parity import TOL, rel_l2
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype", [synth.DTYPE_BF16, synth.DTYPE_FP32])
 # tokens: one row short of and past tile edges, below one tile, and the
 # ragged geometry; batches reach from 32 x 32 tiles to 256 x 256 ones
-@pytest.mark.parametrize("model,grid,batches", [
+GRIDS = [
     ("tiny", (1, 3, 5), (1, 2, 5, 64)),            # 15 rows: less than any tile; K of one and two slices
     ("ragged", (3, 9, 11), (1, 3, 17, 90)),        # 297 rows
     ("wan_mid", (1, 5, 13), (1, 2, 31)),           # 65 rows: one past a 64-row tile; K = 8960 is 140 slices
     ("wan_mid", (3, 8, 16), (1, 4, 9, 33)),        # 384 rows to 12,672: 64 to 256-row tiles
-])
+]
+# 391 rows, an odd number: 192, 224 and 256-row tiles whose waves store their rows
+# and the transposed values through LDS (tests/test_gemm_tile_choice.py holds both
+# lists to the library's tile choice)
+STAGED_GRIDS = [
+    ("wan_mid", (1, 17, 23), (1, 6, 7, 13)),
+    ("wan5b_mid", (1, 17, 23), (1, 2, 3)),
+    ("wan14b_mid", (1, 17, 23), (1, 2, 4)),
+]
+
+
+@pytest.mark.parametrize("dtype", [synth.DTYPE_BF16, synth.DTYPE_FP32])
+@pytest.mark.parametrize("model,grid,batches", GRIDS)
 def test_velocity_is_bitwise_the_same_at_every_batch_size(model, grid, batches, dtype):
     same_at_every_batch_size(model, grid, batches, dtype)
+
+
+@pytest.mark.parametrize("model,grid,batches", STAGED_GRIDS)
+def test_velocity_is_bitwise_the_same_with_large_tiles(model, grid, batches):
+    same_at_every_batch_size(model, grid, batches, synth.DTYPE_BF16)
 
 
 # fp32 attention at head dims 32 and 64: one stream takes one block of 32 queries
