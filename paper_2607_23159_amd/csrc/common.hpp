@@ -38,13 +38,9 @@ template <> struct Mfma32<bf16> {
 };
 
 template <> struct Mfma32<float> {
-  static constexpr int KPL = 1;
-  static constexpr int KSTEP = 2;
-  typedef float frag;
-  static CS_DEV f32x16 mma(frag a, frag b, f32x16 c) {
+  static CS_DEV f32x16 mma(float a, float b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
   }
-  static CS_DEV frag load(const float* p) { return *p; }
 };
 
 // Accumulator register j -> row offset inside the 32x32 tile for lane l.
@@ -54,11 +50,6 @@ template <typename T> CS_DEV T to_t(float v);
 template <> CS_DEV bf16 to_t<bf16>(float v) { return (bf16)v; }
 template <> CS_DEV float to_t<float>(float v) { return v; }
 template <typename T> CS_DEV float to_f(T v) { return (float)v; }
-
-// 16-byte copy helpers.
-struct alignas(16) Chunk16 { uint32_t w[4]; };
-CS_DEV Chunk16 ld16(const void* p) { return *reinterpret_cast<const Chunk16*>(p); }
-CS_DEV void st16(void* p, Chunk16 c) { *reinterpret_cast<Chunk16*>(p) = c; }
 
 // GELU, tanh form: 0.5 x (1 + tanh(u)), u = sqrt(2/pi) (x + 0.044715 x^3).
 // Since 0.5 (1 + tanh(u)) = 1 / (1 + e^(-2u)), it is evaluated as
@@ -102,21 +93,17 @@ CS_DEV int xcd_contiguous(int bid, int nwg) {
   return x * per + min(x, rem) + (bid >> 3);
 }
 
-// ---- direct global->LDS loads (gfx950 global_load_lds_dwordx4): each
-// wave instruction moves 64 x 16 bytes into 1 KB of LDS at base + 16*lane,
-// with an arbitrary global address per lane.
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) void gbl_void_t;
-
-// The same through the buffer path (buffer_load_dwordx4 ... lds): a raw
-// buffer descriptor over [base, base + bytes) and a 32-bit per-lane byte
-// offset voff plus a wave-uniform byte offset soff.  Lanes whose 16 bytes do
-// not lie inside the range receive zeros without any memory access.  The
-// address unit handles a 32-bit offset per lane instead of a 64-bit address,
-// which measured 3-10% faster in the GEMM main loop.  Kept out of lambdas:
-// the builtins exist for the device pass only.
+// ---- direct global->LDS loads (gfx950 buffer_load_dwordx4 ... lds): each
+// wave instruction moves 64 x 16 bytes into 1 KB of LDS at base + 16*lane.  The
+// source is a raw buffer descriptor over [base, base + bytes) and a 32-bit
+// per-lane byte offset voff plus a wave-uniform byte offset soff.  Lanes whose
+// 16 bytes do not lie inside the range receive zeros without any memory access.
+// The address unit handles a 32-bit offset per lane instead of the 64-bit address
+// of a global load, which measured 3-10% faster in the GEMM main loop.  Kept out
+// of lambdas: the builtins exist for the device pass only.
 __device__ __forceinline__ void buffer_load_lds16(const void* base, int bytes, void* lds, int voff,
                                                   int soff) {
+  typedef __attribute__((address_space(3))) void lds_void_t;
   // dword 3 of the descriptor: 32-bit data format, no swizzle, raw access
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes,
                                                                      0x00020000);

@@ -977,7 +977,8 @@ static cs_status step_impl(cs_rollout* r, int32_t step) {
   hipStream_t st = m->stream;
   const cs_rollout_desc& d = r->desc;
   // the decision kernel left the computed streams (and their text branch)
-  // compacted on the device; only their count was read back
+  // compacted on the device; their count is known here, from the kernel or from
+  // the host's own copy of the rule (decide_impl), which must match it
   if (d.mode == CS_CACHE_PAB) {
     // every call computes (the decision compacted all S streams in order);
     // the attention branches follow the broadcast schedule
