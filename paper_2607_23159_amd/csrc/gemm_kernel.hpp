@@ -369,12 +369,18 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_w4(const bf16* __restrict__ A
 // with 128 x 128 ring tiles (three slices ahead) against 94 us with k_gemm_w4's
 // (one and a half), 384 x 4608 x 1536 13.7 us with 64 x 128 against 17.9 us.
 //
-// In fp32 a 32 x 32 x 32 slice of products takes 256 cycles per CU, ten times
-// the fragment reads, and the matrix pipe is the limit whatever the tile: the
-// smallest tile wins by filling the chip evenly, with four workgroups per CU
-// covering each other's barriers.  768 x 1536 x 8960: 183 us (115 TFLOP/s),
-// against 391 us (up to 660) with 128 x 128 register-staged tiles; 1024 x 128 x
-// 512: 5.1 against 43 us.  A lane's 16-byte chunk holds four consecutive k;
+// In bf16 the counters of such launches (384 and 1,536 rows) show neither pipe
+// busy on the CUs that have a tile: products 16 to 40% of the cycles, LDS reads 24
+// to 30%, no bank conflicts, waves waiting for the LDS 5 to 8% of their time.
+//
+// In fp32 a 32 x 32 x 32 slice of products takes 256 cycles per CU, four times
+// what the counters show for its fragment reads (matrix pipe busy 61% of all
+// cycles against 15% at 768 x 1536 x 8960), and the matrix pipe is the limit once
+// the chip is full: 88 to 90% busy with 64 x 64 tiles at 12,480 rows.  Below that
+// the last round counts: the smallest tile wins by filling the chip evenly, with
+// four workgroups per CU covering each other's barriers.  768 x 1536 x 8960: 183 us
+// (115 TFLOP/s), against 391 us (up to 660) with 128 x 128 register-staged tiles;
+// 1024 x 128 x 512: 5.1 against 43 us.  A lane's 16-byte chunk holds four consecutive k;
 // product e of a chunk takes element e of the four lanes of a row, so four
 // products consume a chunk of each operand without any shuffle.  The distance
 // of whole evaluations and rollouts to 64-bit results (8 shapes, 8 seeds each)

@@ -11,7 +11,8 @@ enum Bf16Tile {
 
 // Time of a launch per tile shape, in us:
 //   fixed + rounds * (K/64 * full + epi) + K/64 * (lone + (full - lone) * r) + epi * (1 + r) / 2
-// where a round fills `slots` workgroups on each of the 256 CUs, r is the
+// where a round fills `slots` workgroups on each of the 256 CUs of a whole device
+// (another count changes the speed of the choice, not a result), r is the
 // filled part of the last round (left out when 0), `lone` and `full` are the
 // time per K slice of 64 of a tile alone on its CU and of a full chip, and epi
 // grows by epi_res for residual updates.  The constants are a least-squares fit
@@ -20,12 +21,15 @@ enum Bf16Tile {
 // on another copy of the weights out of 900 MB: in a model a layer's weights
 // come from HBM, which shifts the choice towards shapes with more loads in
 // flight.  They were then adjusted for the choice rather than for the times:
-// against the best tile of each shape it costs 1.0% on average below 1,024 rows
-// or so (at most 20%, at launches of 20 us) and 0.6% above, where 256 x 256
-// tiles for everything took 3.2 times and 12% longer on average.  The row counts
-// between 128 and 256 are for the last round: 12,480 x 1536 x 8960 takes 384 us
-// with 256 rows (294 workgroups on 256 CUs), 315 with 192 and 297 with 160 (468,
-// two nearly full rounds), 12,480 x 4608 x 1536 154 us with 256 and 144 with 224.
+// against the best tile of each of these shapes (none was held out) it costs 1.0%
+// on average below 1,024 rows or so (at most 20%, at launches of 20 us) and 0.6%
+// above, where 256 x 256 tiles for everything took 3.2 times and 12% longer on
+// average.  A 128 x 256 tile is not among them, though at width 5120 it measured 4
+// to 8% faster than the tile chosen (1024 x 5120 x 13824 190 against 205 us, 3120 x
+// 5120 x 5120 152 against 160).  The row counts between 128 and 256 are for the
+// last round: 12,480 x 1536 x 8960 takes 384 us with 256 rows (294 workgroups on
+// 256 CUs), 315 with 192 and 297 with 160 (468, two nearly full rounds), 12,480 x
+// 4608 x 1536 154 us with 256 and 144 with 224.
 struct TileCost { int bm, bn, slots; double lone, full, fixed, epi, epi_res; };
 static constexpr TileCost TILE_COST[N_TILES] = {
     {256, 256, 1, 1.022, 1.378, 3.20, 6.88, 16.20},

@@ -99,9 +99,14 @@ static hipError_t launch_flash_pad(const AttnArgs<bf16>& a, hipStream_t st) {
   // stored 16 bytes at a time
   if (a.vt_ld < round_up(a.lk, 64) || a.o_ld % 8 || a.o_ss % 8) return hipErrorInvalidValue;
   // Estimated time: rounds of the CUs x queries per workgroup x time per query
-  // against 12 waves (8 waves 6%, 4 waves 55% more: 5.33, 5.58 and 7.74 ms for
-  // one stream in whole rounds).  A partly filled last round costs at least 0.7
-  // of a full one (12 waves, 4.03 rounds: 6.29 ms).
+  // against 12 waves; a partly filled last round costs at least 0.7 of a full one.
+  // In whole rounds (49,152 tokens, 12 heads of 128) 12, 8 and 4 waves take 11.1,
+  // 12.1 and 17.4 ms: 9% and 57% more.  8 waves are weighted with 6% instead, for
+  // their last rounds: at 2 x 32,760 tokens, 12 whole rounds of 8 waves and 8.06 of
+  // 12, they take 10.8 against 10.9 ms, at 4 x 32,760 tokens of 4 x 64 heads 4.2
+  // against 4.7.  Over 40 shapes (96 to 49,152 tokens, 1 to 8 streams, 4, 12 and 40
+  // heads of 64 and 128) the choice costs 0.2% on average against the best of the
+  // three, with 9% in its place 0.5%.
   const long cus = cu_count(), sh = (long)a.heads * a.n_streams;
   auto cost = [&](int queries, double per_query) {
     const long nwg = (long)cdiv(a.lq, queries) * sh;
